@@ -229,8 +229,7 @@ int lbp_run_bp(lbp_graph *g, int32_t iters, float damping, float temperature) {
         }
     }
     if (!g->use_resident)
-        e = run_loop(g->ctx, g->loops, g->dgraph, g->use_fused ? g->fused : nullptr, g->vl, g->fl, iters, damping,
-                     temperature);
+        e = run_graph(g, iters, damping, temperature);
     if (e != hipSuccess) return hip_error(e, "iteration launch");
     g->last_T = temperature;
     return LBP_OK;
@@ -278,8 +277,7 @@ int lbp_run_bp_until(lbp_graph *g, int32_t max_iters, float damping, float tempe
         const int32_t c = std::min(check_every, max_iters - done);
         hipError_t e = hipSuccess;
         if (c > 1)
-            e = run_loop(g->ctx, g->loops, g->dgraph, g->use_fused ? g->fused : nullptr, g->vl, g->fl, c - 1, damping,
-                         temperature);
+            e = run_graph(g, c - 1, damping, temperature);
         if (e == hipSuccess) e = hipMemcpyAsync(mprev, g->host.m, sizeof(float) * g->M, hipMemcpyDeviceToDevice, st);
         if (e == hipSuccess) e = run_loop(g->ctx, g->loops, g->dgraph, nullptr, g->vl, g->fl, 1, damping, temperature);
         if (e == hipSuccess) e = launch_residual(g->dgraph, (int)g->E, mprev, partial, res, st);
@@ -681,10 +679,9 @@ int lbp_autotune(lbp_graph *g, float damping, float temperature, int32_t reps, f
         if (x == hipSuccess) x = hipEventElapsedTime(&tr, a, b);
         // launched iterations as lbp_run_bp runs them: a captured loop,
         // captured on the first call and replayed on the timed one
-        const DevGraph *fz = g->use_fused ? g->fused : nullptr;
-        if (x == hipSuccess) x = run_loop(g->ctx, g->loops, g->dgraph, fz, g->vl, g->fl, 2 * reps, damping, temperature);
+        if (x == hipSuccess) x = run_graph(g, 2 * reps, damping, temperature);
         if (x == hipSuccess) x = hipEventRecord(a, st);
-        if (x == hipSuccess) x = run_loop(g->ctx, g->loops, g->dgraph, fz, g->vl, g->fl, 2 * reps, damping, temperature);
+        if (x == hipSuccess) x = run_graph(g, 2 * reps, damping, temperature);
         if (x == hipSuccess) x = hipEventRecord(b, st);
         if (x == hipSuccess) x = hipEventSynchronize(b);
         if (x == hipSuccess) x = hipEventElapsedTime(&tl, a, b);
@@ -727,8 +724,7 @@ int lbp_run_bp_record(lbp_graph *g, int32_t iters, float damping, float temperat
             rc = adjoint_checkpoint(g, sidx, st);
             if (rc != LBP_OK) return rc;
             const int32_t len = std::min(k, iters - sidx * k);
-            hipError_t e = run_loop(g->ctx, g->loops, g->dgraph, g->use_fused ? g->fused : nullptr, g->vl, g->fl, len,
-                                    damping, temperature);
+            hipError_t e = run_graph(g, len, damping, temperature);
             if (e != hipSuccess) return hip_error(e, "recorded iteration launch");
         }
         g->last_T = temperature;

@@ -41,6 +41,25 @@ struct SolvePlan {
 };
 __host__ __device__ constexpr int64_t solve_words_aligned(int64_t w) { return (w + 3) & ~int64_t(3); }
 
+// A graph in the one-workgroup solver of small pairwise graphs: one dense
+// class of n x n states, variables on the lane or wavefront path.
+constexpr int kPairSolveThreads = 1024;
+struct PairSolve {
+    int32_t n = 0;               // states (0: does not apply)
+    int32_t ntiles, nvt, nmid;   // factor tiles, variable tiles, wavefront-path variables (hvar 0 .. nmid - 1)
+    int32_t waves;               // wavefronts of the workgroup
+    int32_t M, B, vedge, zero;   // message and belief floats, edge-list entries held in LDS; the zero panel
+    int32_t lds;                 // floats of LDS
+    int32_t maxdeg;              // longest lane-path edge list
+};
+// factor tiles one wavefront can hold (table registers)
+constexpr int pair_solve_tiles_per_wave(int n) { return n <= 2 ? 8 : n <= 3 ? 4 : n <= 5 ? 2 : 1; }
+inline int32_t pair_solve_lds(const PairSolve &S) {
+    return S.M + S.B + S.nmid * S.n + (S.nmid * kLanes + S.vedge + 1) / 2;
+}
+hipError_t launch_solve_pair(const DevGraph *g, const PairSolve &S, int32_t iters, bool maxp, const TParams &P,
+                             hipStream_t st);
+
 // Launch shape of a wavefront-per-item kernel: wavefronts per block (1, 2 or
 // 4), whether blocks are remapped so each XCD takes a contiguous range, and
 // (fused pairwise launches only) whether tables are loaded before the belief

@@ -26,6 +26,7 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -257,8 +258,8 @@ __device__ __forceinline__ float msg_state(PT p, int n, int s) {
 }
 
 // damp, normalise and store one message row of n states held in registers
-template <int N>
-__device__ __forceinline__ void damp_store(float *row, const float (&mo)[N], const float (&u)[N], int n,
+template <int N, class PT>
+__device__ __forceinline__ void damp_store(PT row, const float (&mo)[N], const float (&u)[N], int n,
                                            const TParams &P) {
     float mn[N];
     float mx = -INFINITY;
@@ -565,6 +566,57 @@ __global__ __launch_bounds__(256) void k_belief(const DevGraph *__restrict__ gs,
 // --------------------------------------------------------------------------
 // factor phase: dense pairwise enumeration factors (one lane per factor)
 // --------------------------------------------------------------------------
+// The update itself: u0[i] = LSE_T,j (p[i][j] + x1[j]) and
+// u1[j] = LSE_T,i (p[i][j] + x0[i]) over na x nb entries.
+template <int NA, int NB, bool MAXP>
+__device__ __forceinline__ void pair_update(const float (&p)[NA][NB], const float (&x0)[NA], const float (&x1)[NB],
+                                            int na, int nb, const TParams &P, float (&u0)[NA], float (&u1)[NB]) {
+    // to slot 0
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+        if (i < na) {
+            float t[NB];
+            float M = -INFINITY;
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                if (j < nb) {
+                    t[j] = p[i][j] + x1[j];
+                    M = fmaxf(M, t[j]);
+                }
+            if (MAXP) {
+                u0[i] = M;
+            } else {
+                float s = 0.0f;
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+                    if (j < nb) s += fexp2((t[j] - M) * P.c);
+                u0[i] = M + flog2(s) * P.r;
+            }
+        }
+    // to slot 1
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+        if (j < nb) {
+            float t[NA];
+            float M = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                if (i < na) {
+                    t[i] = p[i][j] + x0[i];
+                    M = fmaxf(M, t[i]);
+                }
+            if (MAXP) {
+                u1[j] = M;
+            } else {
+                float s = 0.0f;
+#pragma unroll
+                for (int i = 0; i < NA; ++i)
+                    if (i < na) s += fexp2((t[i] - M) * P.c);
+                u1[j] = M + flog2(s) * P.r;
+            }
+        }
+}
+
 // u0[i] = LSE_T,j (phi(i,j) + n1[j]),  u1[j] = LSE_T,i (phi(i,j) + n0[i]);
 // equal to LSE over the configurations with that slot fixed, minus the slot's
 // own incoming term.  EXACT: NA x NB known at compile time; otherwise the
@@ -627,50 +679,7 @@ __device__ __forceinline__ void pair_tile(const GV &G, const FTile &ft, int lane
     }
     if (!EARLY) load_table();
     float u0[NA], u1[NB];
-    // to slot 0
-#pragma unroll
-    for (int i = 0; i < NA; ++i)
-        if (i < na) {
-            float t[NB];
-            float M = -INFINITY;
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-                if (j < nb) {
-                    t[j] = p[i][j] + x1[j];
-                    M = fmaxf(M, t[j]);
-                }
-            if (MAXP) {
-                u0[i] = M;
-            } else {
-                float s = 0.0f;
-#pragma unroll
-                for (int j = 0; j < NB; ++j)
-                    if (j < nb) s += fexp2((t[j] - M) * P.c);
-                u0[i] = M + flog2(s) * P.r;
-            }
-        }
-    // to slot 1
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-        if (j < nb) {
-            float t[NA];
-            float M = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < NA; ++i)
-                if (i < na) {
-                    t[i] = p[i][j] + x0[i];
-                    M = fmaxf(M, t[i]);
-                }
-            if (MAXP) {
-                u1[j] = M;
-            } else {
-                float s = 0.0f;
-#pragma unroll
-                for (int i = 0; i < NA; ++i)
-                    if (i < na) s += fexp2((t[i] - M) * P.c);
-                u1[j] = M + flog2(s) * P.r;
-            }
-        }
+    pair_update<NA, NB, MAXP>(p, x0, x1, na, nb, P, u0, u1);
     damp_store<NA>(w0, m0, u0, na, P);
     damp_store<NB>(w1, m1, u1, nb, P);
 }
@@ -1035,6 +1044,168 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_resident(const DevGraph
         __syncthreads();
     }
     for (int i = tid; i < plan.words[SA_M]; i += kSolveThreads) Gg.m[i] = G.m[i];
+}
+
+// --------------------------------------------------------------------------
+// small pairwise graphs: every iteration in one workgroup
+// --------------------------------------------------------------------------
+// One workgroup keeps a whole graph of dense N x N factors (degrees up to
+// kMidDegMax): each lane holds its factors' tables, messages' positions and
+// slot beliefs' positions in registers (wave w has factor tiles w, w + nw, ...
+// and variable tiles likewise), messages and beliefs sit in LDS in their
+// panel layout, and an iteration is the two phases with a workgroup barrier
+// after each.  Nothing is read from memory inside the loop, and the only
+// indirect LDS reads are those of the edge lists (the first four edges of a
+// lane-path variable are in registers).  Additions and updates are those of
+// belief_low_tile, belief_mid_var and pair_tile in their order, so results
+// are bitwise those of launched iterations.
+// Bound by the one compute unit's instruction issue and LDS latency; launched
+// iterations cost 3 us (fused) or 4.5 us (two launches) whatever the size, so
+// small graphs win here (pair_solve_wins draws the line).  Measured per
+// iteration, launched against this: Ising 32 x 32 at T = 0 3.0 / 0.85 us and
+// at T = 1 3.1 / 1.7; Potts 16 x 16, 5 states at T = 1 4.0 / 1.9; chain of 500
+// 4-state variables at T = 1 3.3 / 1.4; bipartite 20 x 20 at T = 0.05
+// 4.4 / 1.4.
+template <int N, bool MAXP, int FPT>
+__global__ __launch_bounds__(kPairSolveThreads) void k_solve_pair(const DevGraph *__restrict__ gs, PairSolve S,
+                                                                  int iters, TParams P) {
+    extern __shared__ __align__(16) float plds[];
+    constexpr int VPT = 2, KR = 4, MU = 4;
+    const GGraph G = glob(gs[0]);
+    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, nw = nthr >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float *m = plds, *B = m + S.M, *thm = B + S.B;
+    uint16_t *hl = reinterpret_cast<uint16_t *>(thm + S.nmid * N), *vl = hl + S.nmid * kLanes;
+    for (int i = tid; i < S.M; i += nthr) m[i] = G.m[i];
+    for (int i = tid; i < S.vedge; i += nthr) vl[i] = (uint16_t)G.vedge[i];
+    // edge lists and evidence of the wavefront-path variables; a lane past
+    // the last edge points at the zero panel
+    for (int i = tid; i < S.nmid * kLanes; i += nthr) {
+        const HVar h = G.hvar[i >> 6];
+        const int k = h.e_begin + (i & 63);
+        hl[i] = (uint16_t)(k < h.e_end ? G.hedge[k] : S.zero);
+        if ((i & 63) < N) thm[(i >> 6) * N + (i & 63)] = G.theta[h.b_addr + (i & 63) * kLanes];
+    }
+    // this lane's variables
+    int vb[VPT], kmax[VPT], ve[VPT], va[VPT][KR];
+    bool vok[VPT];
+    float th[VPT][N];
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) {
+        const int t = wave + j * nw;
+        vok[j] = false;
+        kmax[j] = 0;
+        if (t >= S.nvt) continue;
+        const VTile vt = G.vtile[t];
+        vok[j] = G.vns[t * kLanes + lane] == N;  // others are not on the lane path, or in no factor
+        vb[j] = vt.b_off + lane;
+        kmax[j] = vt.kmax;
+        ve[j] = vt.e_off + lane;
+#pragma unroll
+        for (int k = 0; k < KR; ++k) va[j][k] = k < vt.kmax ? G.vedge[ve[j] + k * kLanes] : S.zero;
+#pragma unroll
+        for (int s = 0; s < N; ++s) th[j][s] = vok[j] ? G.theta[vb[j] + s * kLanes] : 0.0f;
+    }
+    // this lane's factors
+    float p[FPT][N][N];
+    int o[FPT], b0[FPT], b1[FPT];
+    bool fok[FPT];
+#pragma unroll
+    for (int u = 0; u < FPT; ++u) {
+        const int t = wave + u * nw;
+        fok[u] = false;
+        if (t >= S.ntiles) continue;
+        const FTile ft = G.ftile[t];
+        fok[u] = lane < ft.nact;
+        o[u] = ft.m_off + lane;
+        b0[u] = fok[u] ? G.fvb[ft.vb_off + lane] : 0;
+        b1[u] = fok[u] ? G.fvb[ft.vb_off + kLanes + lane] : 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int j = 0; j < N; ++j) p[u][i][j] = G.phi[ft.phi_off + lane + (i * N + j) * kLanes];
+    }
+    constexpr int MODE = N == 2 ? 2 : 0;
+    __syncthreads();
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+        for (int j = 0; j < VPT; ++j) {
+            if (wave + j * nw >= S.nvt) break;  // uniform
+            float acc[N], x[KR][N];
+#pragma unroll
+            for (int s = 0; s < N; ++s) acc[s] = th[j][s];
+#pragma unroll
+            for (int k = 0; k < KR; ++k) msg_load<N, MODE>(m + va[j][k], N, 0, true, x[k]);
+#pragma unroll
+            for (int k = 0; k < KR; ++k)
+#pragma unroll
+                for (int s = 0; s < N; ++s)
+                    if (k < kmax[j]) acc[s] += x[k][s];
+            for (int k0 = KR; k0 < kmax[j]; k0 += KR) {
+                int a[KR];
+#pragma unroll
+                for (int k = 0; k < KR; ++k) a[k] = k0 + k < kmax[j] ? vl[ve[j] + (k0 + k) * kLanes] : S.zero;
+#pragma unroll
+                for (int k = 0; k < KR; ++k) msg_load<N, MODE>(m + a[k], N, 0, true, x[k]);
+#pragma unroll
+                for (int k = 0; k < KR; ++k)
+#pragma unroll
+                    for (int s = 0; s < N; ++s)
+                        if (k0 + k < kmax[j]) acc[s] += x[k][s];
+            }
+            if (vok[j]) {
+#pragma unroll
+                for (int s = 0; s < N; ++s) B[vb[j] + s * kLanes] = acc[s];
+            }
+        }
+        // wavefront path, MU variables at a time
+        for (int h0 = wave * MU; h0 < S.nmid; h0 += nw * MU) {
+            float x[MU][N];
+#pragma unroll
+            for (int j = 0; j < MU; ++j) {
+                const int h = min(h0 + j, S.nmid - 1);
+                msg_load<N, MODE>(m + hl[h * kLanes + lane], N, 0, true, x[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < MU; ++j)
+#pragma unroll
+                for (int s = 0; s < N; ++s) x[j][s] = wave_sum(x[j][s]);
+#pragma unroll
+            for (int j = 0; j < MU; ++j) {
+                const int h = h0 + j;
+                if (h >= S.nmid) break;
+                float v = 0.0f;
+#pragma unroll
+                for (int s = 0; s < N; ++s)
+                    if (s == lane) v = x[j][s];
+                if (lane < N) B[G.hvar[h].b_addr + lane * kLanes] = thm[h * N + lane] + v;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < FPT; ++u) {
+            if (wave + u * nw >= S.ntiles) break;  // uniform
+            float m0[N], m1[N], x0[N], x1[N], u0[N], u1[N];
+            msg_load<N, MODE>(m + o[u], N, 0, true, m0);
+            msg_load<N, MODE>(m + o[u] + N * kLanes, N, 0, true, m1);
+#pragma unroll
+            for (int s = 0; s < N; ++s) {
+                x0[s] = B[b0[u] + s * kLanes] - m0[s];
+                x1[s] = B[b1[u] + s * kLanes] - m1[s];
+            }
+            pair_update<N, N, MAXP>(p[u], x0, x1, N, N, P, u0, u1);
+            damp_store<N>(m + o[u], m0, u0, N, P);
+            damp_store<N>(m + o[u] + N * kLanes, m1, u1, N, P);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < FPT; ++u) {
+        if (!fok[u]) continue;
+#pragma unroll
+        for (int r = 0; r < 2 * N; ++r)
+            if (N > 2 || r % 2 == 0) G.m[o[u] + r * kLanes] = m[o[u] + r * kLanes];  // (a packed slot's second row is unused)
+    }
 }
 
 // --------------------------------------------------------------------------
@@ -1822,6 +1993,51 @@ hipError_t launch_solve_resident(const DevGraph *g, const SolvePlan &plan, int32
     if (maxp) hipLaunchKernelGGL((k_solve_resident<true>), dim3(1), dim3(kSolveThreads), lds, st, g, plan, iters, P);
     else hipLaunchKernelGGL((k_solve_resident<false>), dim3(1), dim3(kSolveThreads), lds, st, g, plan, iters, P);
     return hipGetLastError();
+}
+
+template <int N, bool MAXP>
+static hipError_t pair_solve_launch(const DevGraph *g, const PairSolve &S, int32_t iters, const TParams &P,
+                                    hipStream_t st) {
+    constexpr int FMAX = pair_solve_tiles_per_wave(N);
+    const size_t shm = sizeof(float) * (size_t)S.lds;
+    auto go = [&](auto fpt) {
+        constexpr int F = decltype(fpt)::value;
+        const void *fn = (const void *)k_solve_pair<N, MAXP, F>;
+        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_solve_pair<N, MAXP, F>), dim3(1), dim3(64 * S.waves), shm, st, g, S, iters, P);
+        return hipGetLastError();
+    };
+    const int f = (S.ntiles + S.waves - 1) / S.waves;
+    if (f <= 1) return go(std::integral_constant<int, 1>());
+    if constexpr (FMAX >= 2)
+        if (f <= 2) return go(std::integral_constant<int, 2>());
+    if constexpr (FMAX >= 4)
+        if (f <= 4) return go(std::integral_constant<int, 4>());
+    if constexpr (FMAX >= 8)
+        if (f <= 8) return go(std::integral_constant<int, 8>());
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_solve_pair(const DevGraph *g, const PairSolve &S, int32_t iters, bool maxp, const TParams &P,
+                             hipStream_t st) {
+    if (iters <= 0) return hipSuccess;
+    if (S.waves < 1 || S.waves > kPairSolveThreads / 64 || S.nvt > 2 * S.waves || S.M >= 65536 ||
+        S.ntiles > S.waves * pair_solve_tiles_per_wave(S.n) || S.lds != pair_solve_lds(S))
+        return hipErrorInvalidValue;
+    switch (S.n) {
+#define SOLVE_CASE(K) \
+    case K: return maxp ? pair_solve_launch<K, true>(g, S, iters, P, st) : pair_solve_launch<K, false>(g, S, iters, P, st);
+        SOLVE_CASE(2)
+        SOLVE_CASE(3)
+        SOLVE_CASE(4)
+        SOLVE_CASE(5)
+        SOLVE_CASE(6)
+        SOLVE_CASE(7)
+        SOLVE_CASE(8)
+#undef SOLVE_CASE
+    default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_logical(const DevGraph *gs, const WorkItem *items, int n, bool wide, bool maxp, const TParams &P,

@@ -493,6 +493,7 @@ int graph_create(lbp_ctx *ctx, const HostLayout &L, bool with_fused, char *mem, 
         g->V = L.V; g->VS = L.VS; g->F = L.F; g->E = L.E; g->ES = L.ES; g->Tn = L.Tn;
         g->M = L.M; g->VB = L.VB; g->P = L.P;
         g->nvt = (int32_t)L.vtile.size();
+        make_pair_solve(L, solve_lds_limit(ctx->device) / 4, &g->small);
         g->resident_ok = make_solve_plan(g->vl, g->fl, L, solve_lds_limit(ctx->device) / 4, &g->plan);
         *out = g;
         return LBP_OK;
@@ -535,6 +536,68 @@ bool make_solve_plan(const std::vector<Launch> &vl, const std::vector<Launch> &f
     }
     *plan = p;
     return true;
+}
+
+bool make_pair_solve(const HostLayout &L, int64_t limit_words, PairSolve *plan) {
+    *plan = PairSolve{};
+    if (L.fgroups.size() != 1 || L.fgroups[0].kind != TK_PAIR || L.fgroups[0].a != L.fgroups[0].b ||
+        L.fgroups[0].a > kPairStatesMax || !L.highs.empty() || !L.cols.empty() ||
+        L.mids.size() != L.hvar.size() || L.fgroups[0].tiles.size() != L.ftile.size())
+        return false;
+    PairSolve S;
+    S.n = L.fgroups[0].a;
+    const int64_t nt = (int64_t)L.ftile.size(), nvt = (int64_t)L.vtile.size(), nmid = (int64_t)L.hvar.size();
+    const int64_t maxw = kPairSolveThreads / 64, B = L.VB - (int64_t)kLanes * kMaxStates;  // without the spare panel
+    if (nt > maxw * pair_solve_tiles_per_wave(S.n) || nvt > 2 * maxw || nmid > 4096 || L.M >= 65536) return false;
+    S.ntiles = (int32_t)nt;
+    S.nvt = (int32_t)nvt;
+    S.nmid = (int32_t)nmid;
+    // a wavefront per tile while there are that many
+    const int64_t w = std::max({(nt + pair_solve_tiles_per_wave(S.n) - 1) / pair_solve_tiles_per_wave(S.n),
+                                std::min(maxw, nt), (nvt + 1) / 2, std::min(maxw, (nmid + 3) / 4), int64_t(1)});
+    S.waves = (int32_t)std::min(maxw, w);
+    S.M = (int32_t)L.M;
+    S.B = (int32_t)B;
+    S.zero = L.zero_addr;
+    S.maxdeg = 0;
+    for (const VTile &vt : L.vtile) S.maxdeg = std::max(S.maxdeg, vt.kmax);
+    S.vedge = S.maxdeg > 4 ? (int32_t)L.vedge.size() : 0;
+    S.lds = pair_solve_lds(S);
+    if (S.lds > limit_words) return false;
+    *plan = S;
+    return true;
+}
+
+// Where one workgroup beats launched iterations.  Max-product: wherever the
+// graph fits (slowest seen: a 64 x 64 bipartite layer, 4.1 against 4.6 us per
+// iteration; Potts 22 x 22, 8 states 2.3 against 4.4).  Sums: the workgroup's
+// cycles, estimated from the busiest SIMD's factor tiles (per table entry an
+// add, a subtraction, a multiplication, an exponential and an add, exponentials
+// at a quarter of the rate; the rows' damping) and variable sums, at 3600 of
+// them per us as measured, against what launched iterations take whatever the
+// size of a small graph: 2.9 us and 0.4 more per state above two (fused; the
+// lane's serial chain), 4.5 us for the two launches of a graph with
+// wavefront-path variables.  Measured at T = 1, launched / this, on either
+// side of the line: Potts 24 x 24, 4 states 3.7 / 2.8, 30 x 30 3.8 / 3.9;
+// 20 x 20, 6 states 4.6 / 4.4; 28 x 28, 5 states 4.2 / 5.6; bipartite
+// 50 x 50 4.9 / 3.3, 64 x 64 4.9 / 5.7.
+static bool pair_solve_wins(const PairSolve &S, bool maxp) {
+    if (maxp) return true;
+    const int64_t n = S.n, tiles = (S.ntiles + 3) / 4, vts = (S.nvt + 3) / 4, mids = (S.nmid + 15) / 16;
+    const int64_t tile = 4 * (2 * n * n * 5 + 24 * n) + 16 * (2 * n * n + 2 * n);
+    const int64_t cycles = tiles * tile + vts * 4 * n * (6 + 2 * S.maxdeg) + mids * 4 * (60 + 60 * n) + 1000;
+    return cycles < 340 * (S.nmid ? 45 : 29 + 4 * (n - 2));
+}
+
+hipError_t run_graph(lbp_graph *g, int32_t iters, float d, float T) {
+    if (g->small.n && iters >= 2 && pair_solve_wins(g->small, T == 0.0f)) {
+        const hipError_t e =
+            launch_solve_pair(g->dgraph, g->small, iters, T == 0.0f, make_params(d, T), g->ctx->stream);
+        if (e == hipSuccess) return e;
+        (void)hipGetLastError();  // refused (LDS size): launched iterations from here on
+        g->small.n = 0;
+    }
+    return run_loop(g->ctx, g->loops, g->dgraph, g->use_fused ? g->fused : nullptr, g->vl, g->fl, iters, d, T);
 }
 
 void graph_destroy(lbp_graph *g) {

@@ -122,6 +122,7 @@ struct lbp_graph {
     bool resident_ok = false;         // small enough for the resident solver (plan below)
     bool use_resident = false;        // lbp_run_bp runs the resident solver (chosen by the autotuner)
     lbp::SolvePlan plan;
+    lbp::PairSolve small;             // plan of the one-workgroup solver of small pairwise graphs (n = 0: does not apply)
     float *q_tmp = nullptr;           // VS
     int32_t *map_tmp = nullptr;       // V
     std::vector<lbp::Launch> vl, fl;  // the graph's own launches
@@ -208,6 +209,12 @@ void graph_destroy(lbp_graph *g);
 // the other arrays are placed in LDS in SolveArray order while they fit.
 bool make_solve_plan(const std::vector<Launch> &vl, const std::vector<Launch> &fl, const HostLayout &L,
                      int64_t limit_words, SolvePlan *plan);
+
+// The same for the solver of small pairwise graphs (PairSolve).
+bool make_pair_solve(const HostLayout &L, int64_t limit_words, PairSolve *plan);
+// `iters` iterations of g on its context's stream as lbp_run_bp runs them:
+// small pairwise graphs in one workgroup, others through run_loop.
+hipError_t run_graph(lbp_graph *g, int32_t iters, float d, float T);
 
 // Read-out (beliefs and/or MAP) on `st`; host outputs are copied with
 // hipMemcpyAsync and are complete once `st` is synchronised.
