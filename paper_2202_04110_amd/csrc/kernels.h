@@ -71,12 +71,15 @@ struct LaunchShape {
 };
 
 // Buffers of the reverse sweep (message panels A, nbar; belief panel Bbar;
-// potential panel phibar).
+// potential panel phibar).  Fused steps also take the nbar of the step before
+// (another buffer; null: the first step) and the panel of thetabar.
 struct AdjBufs {
     float *A;
     float *nbar;
     const float *Bbar;
     float *phibar;
+    const float *nbar_in;
+    float *thetabar;
 };
 
 // Variable phase: items = n_low low tiles, then n_mid and n_high variables
@@ -163,7 +166,9 @@ hipError_t launch_logpot_in(const DevGraph *gs, int F, const float *in, hipStrea
 
 // adjoint
 hipError_t launch_pair_adj(const DevGraph *gs, const WorkItem *items, int n, int na, int nb, const TParams &P,
-                           const AdjBufs &J, hipStream_t st);
+                           const AdjBufs &J, hipStream_t st, bool fused = false);
+// view->m = m, on the stream.
+hipError_t launch_set_messages(DevGraph *view, float *m, hipStream_t st);
 hipError_t launch_gen_adj(const DevGraph *gs, const WorkItem *items, int n, const TParams &P, const AdjBufs &J,
                           hipStream_t st);
 hipError_t launch_readout_adj(const DevGraph *gs, int nvtiles, const TParams &P, const float *gq, float *bbar,

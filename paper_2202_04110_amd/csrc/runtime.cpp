@@ -490,6 +490,7 @@ int graph_create(lbp_ctx *ctx, const HostLayout &L, bool with_fused, char *mem, 
         g->shape = GraphShape{L.fgroups, L.vgroups, L.mids, L.highs, L.cols};
         for (const FGroup &fg : L.fgroups)
             if (fg.kind == TK_LOGL || fg.kind == TK_LOGW) g->has_logical = true;
+        g->fusable = L.fusable;
         g->V = L.V; g->VS = L.VS; g->F = L.F; g->E = L.E; g->ES = L.ES; g->Tn = L.Tn;
         g->M = L.M; g->VB = L.VB; g->P = L.P;
         g->nvt = (int32_t)L.vtile.size();
@@ -748,14 +749,37 @@ int adjoint_backward(lbp_graph *g, const float *grad_q, float *grad_logpot, floa
     const TParams P = make_params(J.d, J.T);
     const int64_t M = g->M;
     const int k = J.k;
-    AdjBufs B{J.A, J.nbar, J.Bbar, J.phibar};
-    HIP_TRY(hipMemsetAsync(J.A, 0, sizeof(float) * M, st));
-    HIP_TRY(hipMemsetAsync(J.phibar, 0, sizeof(float) * g->P, st));
+    // Fused form: one launch per recomputed iteration and per reverse step.  A
+    // segment's first iterate is its checkpoint itself, which leaves the first
+    // iterate buffer to the second nbar.
+    const bool fused = g->fusable && J.iters > 0;
+    float *nbar[2] = {J.nbar, J.seg};
+    int cur = 0;  // the nbar written last
+    AdjBufs B{J.A, J.nbar, J.Bbar, J.phibar, nullptr, J.thetabar};
+    if (!fused) {
+        HIP_TRY(hipMemsetAsync(J.A, 0, sizeof(float) * M, st));
+        HIP_TRY(hipMemsetAsync(J.phibar, 0, sizeof(float) * g->P, st));
+    }
     // read-out adjoint at the recorded final iterate (the graph's messages)
     hipError_t e = launch_iteration(J.views + k, g->vl, g->fl, P, false, st, 1);
     if (e == hipSuccess) e = launch_readout_adj(J.views + k, g->nvt, P, grad_q, J.Bbar, J.thetabar, st);
     for (int32_t sidx = J.nseg - 1; sidx >= 0 && e == hipSuccess; --sidx) {
         const int32_t len = std::min(k, J.iters - sidx * k);
+        if (fused) {
+            e = launch_set_messages(J.views, J.ckpt + M * sidx, st);
+            for (int32_t j = 0; j + 1 < len && e == hipSuccess; ++j)
+                for (const Launch &L : g->fl)
+                    if (e == hipSuccess)
+                        e = launch_pair(J.views + j, L.items, L.n, L.a, L.b, false, P, L.fshape, st, true);
+            for (int32_t j = len - 1; j >= 0 && e == hipSuccess; --j) {
+                B.nbar = nbar[cur ^ 1];
+                for (const Launch &L : g->fl)
+                    if (e == hipSuccess) e = launch_pair_adj(J.views + j, L.items, L.n, L.a, L.b, P, B, st, true);
+                cur ^= 1;
+                B.nbar_in = nbar[cur];
+            }
+            continue;
+        }
         e = hipMemcpyAsync(J.seg, J.ckpt + M * sidx, sizeof(float) * M, hipMemcpyDeviceToDevice, st);
         for (int32_t j = 0; j + 1 < len && e == hipSuccess; ++j)
             e = launch_iteration(J.views + j, g->vl, g->fl, P, false, st, 3);
@@ -769,6 +793,12 @@ int adjoint_backward(lbp_graph *g, const float *grad_q, float *grad_logpot, floa
             if (e == hipSuccess) e = launch_iteration(J.views + k + 1, g->vl, g->fl, P, false, st, 1);  // Bbar_t
             if (e == hipSuccess) e = launch_accumulate(J.thetabar, J.Bbar, g->VB, st);
         }
+    }
+    if (fused && e == hipSuccess) {  // Bbar_0, from the view that sums J.nbar or its sibling over J.seg
+        if (cur == 1) e = launch_set_messages(J.views + k + 1, J.seg, st);
+        if (e == hipSuccess) e = launch_iteration(J.views + k + 1, g->vl, g->fl, P, false, st, 1);
+        if (cur == 1 && e == hipSuccess) e = launch_set_messages(J.views + k + 1, J.nbar, st);
+        if (e == hipSuccess) e = launch_accumulate(J.thetabar, J.Bbar, g->VB, st);
     }
     if (e == hipSuccess) e = launch_logpot_out(g->dgraph, (int)g->F, J.phibar, grad_logpot, st);
     if (e == hipSuccess && grad_evidence) e = launch_evidence_out(g->dgraph, (int)g->V, J.thetabar, grad_evidence, st);

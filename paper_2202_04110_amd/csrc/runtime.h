@@ -130,6 +130,7 @@ struct lbp_graph {
     float last_T = 0.0f;
     std::vector<lbp::CachedLoop> loops;
     bool has_logical = false;
+    bool fusable = false;  // lane-path variables and square pairwise factors only
     uint64_t version = 0;  // bumped by every call that changes messages or inputs
     char *conv = nullptr;  // lbp_run_bp_until workspace: previous messages, partial and final residuals
     // reverse-sweep workspace and the record it belongs to
