@@ -291,13 +291,60 @@ __device__ __forceinline__ void damp_store(PT row, const float (&mo)[N], const f
 // wavefront items each (low tiles first, then mid variables), the remaining
 // blocks one high variable each.
 
-// low: NB >= states of every lane; edge rows fetched KU at a time (addresses,
-// then rows, all in flight) and added in edge order.  MODE as for msg_load.
+// Every gather below loads from an address that exists whether or not its
+// lane has an edge there, and takes the value afterwards: a test around each
+// load compiles to a branch each, a wait behind each and no loads in flight
+// together.  Bound by launch and latency at these sizes.  Measured per
+// iteration, tested loads against these: Potts 128 x 128 with 5 states at T = 1
+// (fused) 4.4 / 3.8 us, 512 x 512 17.8 / 17.2, random pairs of 3000 variables
+// 7.1 / 6.2, RBM 784 x 500 8.0 / 7.7, three-way grid 256 x 256 10.7 / 10.5.
+
+// low, tiles whose lanes hold N states or none: straight code for N.  Edge
+// rows are fetched KU at a time (addresses, then rows, all in flight) and
+// added in edge order; the tile's edge-address rows end at kmax, past which
+// the zero panel is read (adding it changes nothing).  MODE as for msg_load.
+// a0: the first four (past four edges: eight) addresses, asked for before the tile's form was known.
+template <int N, int MODE, class GV>
+__device__ __forceinline__ void belief_low_tile_n(const GV &G, const VTile &vt, const int (&a0)[8], int n, int lane) {
+    const int base = vt.b_off + lane;
+    float acc[N];
+#pragma unroll
+    for (int s = 0; s < N; ++s) acc[s] = G.theta[base + s * kLanes];
+    const int32_t *ea = G.vedge + vt.e_off + lane;
+    auto rows = [&](int k0, auto ku) {
+        constexpr int KU = decltype(ku)::value;
+        int a[KU];
+#pragma unroll
+        for (int u = 0; u < KU; ++u) a[u] = k0 == 0 ? a0[u] : ea[min(k0 + u, vt.kmax - 1) * kLanes];
+        float x[KU][N];
+#pragma unroll
+        for (int u = 0; u < KU; ++u)
+            msg_load<N, MODE>(G.m + (k0 + u < vt.kmax ? a[u] : G.zero_addr), N, 0, true, x[u]);
+#pragma unroll
+        for (int u = 0; u < KU; ++u)
+#pragma unroll
+            for (int s = 0; s < N; ++s)
+                if (k0 + u < vt.kmax) acc[s] += x[u][s];
+    };
+    // (grid variables have four edges, product variables of logical graphs two)
+    if (vt.kmax == 1) rows(0, std::integral_constant<int, 1>());
+    else if (vt.kmax == 2) rows(0, std::integral_constant<int, 2>());
+    else if (vt.kmax > 0 && (vt.kmax <= 4 || N > 4)) {
+        rows(0, std::integral_constant<int, 4>());
+        for (int k0 = 4; k0 < vt.kmax; k0 += 4) rows(k0, std::integral_constant<int, 4>());
+    } else if (vt.kmax > 0) {
+        rows(0, std::integral_constant<int, 8>());
+        for (int k0 = 8; k0 < vt.kmax; k0 += 8) rows(k0, std::integral_constant<int, 8>());
+    }
+    if (n != N) return;
+#pragma unroll
+    for (int s = 0; s < N; ++s) G.B[base + s * kLanes] = acc[s];
+}
+
+// low, any tile: NB >= states of every lane
 template <int NB, int MODE, class GV>
-__device__ __forceinline__ void belief_low_tile_m(const GV &G, int t, int lane) {
+__device__ __forceinline__ void belief_low_tile_m(const GV &G, const VTile &vt, int n, int lane) {
     constexpr int KU = NB <= 4 ? 8 : 4;
-    const VTile vt = G.vtile[t];
-    const int n = G.vns[t * kLanes + lane];
     const int base = vt.b_off + lane;
     float acc[NB];
 #pragma unroll
@@ -321,56 +368,77 @@ __device__ __forceinline__ void belief_low_tile_m(const GV &G, int t, int lane) 
         if (s < n) G.B[base + s * kLanes] = acc[s];
 }
 
-// A tile whose panel has two rows holds only two-state variables (and idle
-// lanes): every row it reads is packed.
+// The tile's own code when its variables all have its panel's state count
+// (two-state rows are then packed, except in the reverse sweep's sums), else
+// the general form.
 template <int NB, class GV>
 __device__ __forceinline__ void belief_low_tile(const GV &G, int t, int lane) {
-    if (G.raw_msgs) belief_low_tile_m<NB, 0>(G, t, lane);
-    else if (G.vtile[t].n == 2) belief_low_tile_m<NB, 2>(G, t, lane);
-    else belief_low_tile_m<NB, 1>(G, t, lane);
+    const VTile vt = G.vtile[t];
+    const int n = G.vns[t * kLanes + lane];
+    int a0[8] = {};
+    if (vt.kmax > 0) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a0[u] = G.vedge[vt.e_off + min(u, vt.kmax - 1) * kLanes + lane];
+    }
+    if (vt.kmax > 4 && vt.n <= 4) {
+#pragma unroll
+        for (int u = 4; u < 8; ++u) a0[u] = G.vedge[vt.e_off + min(u, vt.kmax - 1) * kLanes + lane];
+    }
+    const int rows = __builtin_amdgcn_readfirstlane(vt.n);
+    if (rows == 2) {  // two states or none in every lane
+        if (G.raw_msgs) belief_low_tile_n<2, 0>(G, vt, a0, n, lane);
+        else belief_low_tile_n<2, 2>(G, vt, a0, n, lane);
+        return;
+    }
+    if (rows <= NB && __ballot(n != 0 && n != rows) == 0) {
+        if constexpr (NB >= 4) {
+            if (rows == 3) return belief_low_tile_n<3, 0>(G, vt, a0, n, lane);
+            if (rows == 4) return belief_low_tile_n<4, 0>(G, vt, a0, n, lane);
+        }
+        if constexpr (NB >= 8) {
+            if (rows == 5) return belief_low_tile_n<5, 0>(G, vt, a0, n, lane);
+            if (rows == 6) return belief_low_tile_n<6, 0>(G, vt, a0, n, lane);
+            if (rows == 7) return belief_low_tile_n<7, 0>(G, vt, a0, n, lane);
+            if (rows == 8) return belief_low_tile_n<8, 0>(G, vt, a0, n, lane);
+        }
+    }
+    if (G.raw_msgs) belief_low_tile_m<NB, 0>(G, vt, n, lane);
+    else belief_low_tile_m<NB, 1>(G, vt, n, lane);
 }
 
-// The beliefs of two lane-path variables at once (va with na states, vb with
-// nb) in registers, each with belief_low_tile's additions in its order (theta
-// first, then the edges in order); both gathers are in flight together.  mm:
+// The beliefs of two lane-path variables at once (va with NA states, vb with
+// NB: the fused kernels' square classes) in registers, each with
+// belief_low_tile's additions in its order (theta first, then the edges in
+// order); both gathers are in flight together.  mm:
 // the message panels (MODE as for msg_load); THETA: with the evidence, else
 // the messages' sums alone (the reverse sweep).  fa, fb: the first edges'
 // message addresses (-1: none).
+// An idle lane (-1) gathers what the wavefront's first lane does; its
+// result is not used.
 template <int NA, int NB, int MODE, bool THETA, class GV, class PT>
-__device__ __forceinline__ void belief_regs2(const GV &G, PT mm, int va, int na, int vb, int nb,
-                                             float (&ba)[NA], float (&bb)[NB], int &fa, int &fb) {
+__device__ __forceinline__ void belief_regs2(const GV &G, PT mm, int va, int vb, float (&ba)[NA], float (&bb)[NB],
+                                             int &fa, int &fb) {
     constexpr int KU = 4;
+    // (read before the test: under it, the first lane would be an idle one;
+    // lane 0 never is)
+    const int va0 = __builtin_amdgcn_readfirstlane(va), vb0 = __builtin_amdgcn_readfirstlane(vb);
+    va = va < 0 ? va0 : va;
+    vb = vb < 0 ? vb0 : vb;
+    const int la = va & (kLanes - 1), lb = vb & (kLanes - 1);
+    const VTile ta = G.vtile[va >> 6], tb = G.vtile[vb >> 6];
 #pragma unroll
-    for (int s = 0; s < NA; ++s) ba[s] = 0.0f;
+    for (int s = 0; s < NA; ++s) ba[s] = THETA ? G.theta[ta.b_off + la + s * kLanes] : 0.0f;
 #pragma unroll
-    for (int s = 0; s < NB; ++s) bb[s] = 0.0f;
-    const int ka = va >= 0 ? G.vtile[va >> 6].kmax : 0;
-    const int kb = vb >= 0 ? G.vtile[vb >> 6].kmax : 0;
-    const int32_t *ea = nullptr, *eb = nullptr;
-    if (va >= 0) {
-        const VTile vt = G.vtile[va >> 6];
-        const int base = vt.b_off + (va & (kLanes - 1));
-#pragma unroll
-        for (int s = 0; s < NA; ++s)
-            if (THETA && s < na) ba[s] = G.theta[base + s * kLanes];
-        ea = G.vedge + vt.e_off + (va & (kLanes - 1));
-    }
-    if (vb >= 0) {
-        const VTile vt = G.vtile[vb >> 6];
-        const int base = vt.b_off + (vb & (kLanes - 1));
-#pragma unroll
-        for (int s = 0; s < NB; ++s)
-            if (THETA && s < nb) bb[s] = G.theta[base + s * kLanes];
-        eb = G.vedge + vt.e_off + (vb & (kLanes - 1));
-    }
-    const int kmax = ka > kb ? ka : kb;
+    for (int s = 0; s < NB; ++s) bb[s] = THETA ? G.theta[tb.b_off + lb + s * kLanes] : 0.0f;
+    const int32_t *ea = G.vedge + ta.e_off + la, *eb = G.vedge + tb.e_off + lb;
+    const int kmax = max(ta.kmax, tb.kmax);
     fa = fb = -1;
     for (int k0 = 0; k0 < kmax; k0 += KU) {
         int a[KU], b[KU];
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
-            a[u] = (k0 + u < ka) ? ea[(k0 + u) * kLanes] : -1;
-            b[u] = (k0 + u < kb) ? eb[(k0 + u) * kLanes] : -1;
+            a[u] = ea[min(k0 + u, ta.kmax - 1) * kLanes];
+            b[u] = eb[min(k0 + u, tb.kmax - 1) * kLanes];
         }
         if (k0 == 0) {
             fa = a[0];
@@ -379,17 +447,15 @@ __device__ __forceinline__ void belief_regs2(const GV &G, PT mm, int va, int na,
         float x[KU][NA], y[KU][NB];
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
-            msg_load<NA, MODE>(mm + (a[u] >= 0 ? a[u] : 0), na, 0, a[u] >= 0, x[u]);
-            msg_load<NB, MODE>(mm + (b[u] >= 0 ? b[u] : 0), nb, 0, b[u] >= 0, y[u]);
+            msg_load<NA, MODE>(mm + (k0 + u < ta.kmax ? a[u] : G.zero_addr), NA, 0, true, x[u]);
+            msg_load<NB, MODE>(mm + (k0 + u < tb.kmax ? b[u] : G.zero_addr), NB, 0, true, y[u]);
         }
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
 #pragma unroll
-            for (int s = 0; s < NA; ++s)
-                if (a[u] >= 0 && s < na) ba[s] += x[u][s];
+            for (int s = 0; s < NA; ++s) ba[s] += x[u][s];
 #pragma unroll
-            for (int s = 0; s < NB; ++s)
-                if (b[u] >= 0 && s < nb) bb[s] += y[u][s];
+            for (int s = 0; s < NB; ++s) bb[s] += y[u][s];
         }
     }
 }
@@ -401,15 +467,30 @@ __device__ __forceinline__ void belief_mid_var(const GV &G, int hv, int lane) {
     constexpr int SC = 8;
     const HVar h = G.hvar[hv];
     const int k = h.e_begin + lane;
-    const int a = k < h.e_end ? G.hedge[k] : -1;
+    const bool have = k < h.e_end;
+    if (h.e_begin == h.e_end) {  // many states and no edge
+        for (int s = lane; s < h.n; s += kLanes) G.B[h.b_addr + s * kLanes] = G.theta[h.b_addr + s * kLanes] + 0.0f;
+        return;
+    }
+    const int a = G.hedge[have ? k : h.e_begin];
+    if (h.n == 2 && !G.raw_msgs) {  // packed: one value a row
+        const float th = G.theta[h.b_addr + (lane & 1) * kLanes];
+        const float d = G.m[a];
+        const float s0 = wave_sum(pk_m0(have ? d : 0.0f)), s1 = wave_sum(pk_m1(have ? d : 0.0f));
+        if (lane < 2) G.B[h.b_addr + lane * kLanes] = th + (lane ? s1 : s0);
+        return;
+    }
     for (int s0 = 0; s0 < h.n; s0 += SC) {
         // lane j's evidence term, loaded with the edge rows rather than
         // after the sums
         const bool own = lane < SC && s0 + lane < h.n;
         const float th = own ? G.theta[h.b_addr + (s0 + lane) * kLanes] : 0.0f;
         float x[SC];
-        if (G.raw_msgs) msg_load<SC, 0>(G.m + (a >= 0 ? a : 0), h.n, s0, a >= 0, x);
-        else msg_load<SC, 1>(G.m + (a >= 0 ? a : 0), h.n, s0, a >= 0, x);
+#pragma unroll
+        for (int j = 0; j < SC; ++j) {
+            const float v = G.m[a + min(s0 + j, h.n - 1) * kLanes];
+            x[j] = have ? v : 0.0f;
+        }
 #pragma unroll
         for (int j = 0; j < SC; ++j)
             if (s0 + j < h.n) x[j] = wave_sum(x[j]);  // uniform condition
@@ -447,17 +528,31 @@ __device__ __forceinline__ void belief_high_var(const GV &G, int hv, int tid, fl
 #pragma unroll
             for (int u = 0; u < KC; ++u) {
                 const int k = k0 + u * kHighThreads;
-                a[u] = k < h.e_end ? G.hedge[k] : -1;
+                a[u] = G.hedge[min(k, h.e_end - 1)];
             }
-            float x[KC][SC];
+            // (an edge that is not there adds +0: sums start at +0 and are
+            // never -0)
+            if (MODE == 2) {
+                float d[KC];
 #pragma unroll
-            for (int u = 0; u < KC; ++u)
-                msg_load<SC, MODE>(G.m + (a[u] >= 0 ? a[u] : 0), h.n, s0, a[u] >= 0, x[u]);
+                for (int u = 0; u < KC; ++u) d[u] = G.m[a[u]];
 #pragma unroll
-            for (int u = 0; u < KC; ++u)
+                for (int u = 0; u < KC; ++u) {
+                    const float t = k0 + u * kHighThreads < h.e_end ? d[u] : 0.0f;
+                    part[0] += pk_m0(t);
+                    part[1] += pk_m1(t);
+                }
+            } else {
+                float x[KC][SC];
 #pragma unroll
-                for (int j = 0; j < SC; ++j)
-                    if (a[u] >= 0 && j < ns) part[j] += x[u][j];
+                for (int u = 0; u < KC; ++u)
+#pragma unroll
+                    for (int j = 0; j < SC; ++j) x[u][j] = G.m[a[u] + (s0 + min(j, ns - 1)) * kLanes];
+#pragma unroll
+                for (int u = 0; u < KC; ++u)
+#pragma unroll
+                    for (int j = 0; j < SC; ++j) part[j] += k0 + u * kHighThreads < h.e_end ? x[u][j] : 0.0f;
+            }
         }
 #pragma unroll
         for (int j = 0; j < SC; ++j)
@@ -506,17 +601,30 @@ __device__ __forceinline__ void belief_col_group(const GV &G, const HVar &h, int
 #pragma unroll
             for (int u = 0; u < kColRound; ++u) {
                 const int k = k0 + u * KG;
-                a[u] = k < kmax ? G.hedge[h.e_begin + (k << lsh) + l] : -1;
+                const int e = G.hedge[h.e_begin + (min(k, kmax - 1) << lsh) + l];
+                a[u] = k < kmax ? e : -1;
             }
             float x[kColRound][kColStates];
 #pragma unroll
-            for (int u = 0; u < kColRound; ++u)
-                msg_load<kColStates, MODE>(G.m + (a[u] >= 0 ? a[u] : 0), h.n, s0, a[u] >= 0, x[u]);
+            for (int u = 0; u < kColRound; ++u) {
+                const auto row = G.m + (a[u] >= 0 ? a[u] : G.zero_addr);
+                if (MODE == 2) {
+                    x[u][0] = row[0];
+                } else {
 #pragma unroll
-            for (int u = 0; u < kColRound; ++u)
+                    for (int j = 0; j < kColStates; ++j) x[u][j] = row[a[u] >= 0 ? (s0 + min(j, ns - 1)) * kLanes : 0];
+                }
+            }
 #pragma unroll
-                for (int j = 0; j < kColStates; ++j)
-                    if (a[u] >= 0 && j < ns) part[j] += x[u][j];
+            for (int u = 0; u < kColRound; ++u) {
+                if (MODE == 2) {
+                    const float d = x[u][0];
+                    x[u][0] = pk_m0(d);
+                    x[u][1] = pk_m1(d);
+                }
+#pragma unroll
+                for (int j = 0; j < kColStates; ++j) part[j] += x[u][j];
+            }
         }
         const int wave = tid >> 6;
 #pragma unroll
@@ -536,14 +644,19 @@ __device__ __forceinline__ void belief_col_group(const GV &G, const HVar &h, int
     }
 }
 
-template <int NB>
-__global__ __launch_bounds__(256) void k_belief(const DevGraph *__restrict__ gs, const WorkItem *__restrict__ items,
+// HIGH: the launch has block-per-variable items.  Left alone the compiler
+// spends 104 registers on their gathers, which big launches pay for in
+// wavefronts per SIMD (16 deconvolution samples: 19.1 ms against 15.7 held to
+// eight wavefronts, 17.7 before); launches without them need no limit
+// (three-way grid 256 x 256: 10.5 us per iteration against 10.7 with it).
+template <int NB, bool HIGH>
+__global__ __launch_bounds__(256, HIGH && NB <= 8 ? 8 : 1) void k_belief(const DevGraph *__restrict__ gs, const WorkItem *__restrict__ items,
                                                 int n_low, int n_mid, int n_high, int swz) {
-    __shared__ float red[8][kHighWaves];
-    __shared__ float cred[kColRed];
     // block-per-variable items first: they are the longest, so they start
     // before the wavefront items fill the machine
-    if ((int)blockIdx.x < n_high) {
+    if (HIGH && (int)blockIdx.x < n_high) {
+        __shared__ float red[8][kHighWaves];
+        __shared__ float cred[kColRed];
         const int hb = __builtin_amdgcn_readfirstlane((int)blockIdx.x);
         const WorkItem it = items[n_low + n_mid + hb];
         const auto G = glob(gs[it.g]);
@@ -670,7 +783,7 @@ __device__ __forceinline__ void pair_tile(const GV &G, const FTile &ft, int lane
         float b0[NA], b1[NB];
         int va, vb, fa, fb;
         slot_vars(G, ft, lane, t, va, vb);
-        belief_regs2<NA, NB, 1, true>(G, G.m, va, na, vb, nb, b0, b1, fa, fb);
+        belief_regs2<NA, NB, NA == 2 ? 2 : 0, true>(G, G.m, va, vb, b0, b1, fa, fb);
         msg_load<NA, 1>(r0, na, 0, true, m0);
         msg_load<NB, 1>(r1, nb, 0, true, m1);
 #pragma unroll
@@ -1438,15 +1551,15 @@ __global__ __launch_bounds__(256) void k_pair_adj(const DevGraph *__restrict__ g
     if (FUSED) {
         int sa, sb, fa, fb;
         slot_vars(G, ft, lane, it.t, sa, sb);
-        belief_regs2<NA, NB, 1, true>(G, G.m, sa, na, sb, nb, x0, x1, fa, fb);
+        belief_regs2<NA, NB, NA == 2 ? 2 : 0, true>(G, G.m, sa, sb, x0, x1, fa, fb);
         if (!first) {
-            belief_regs2<NA, NB, 0, false>(G, as_global(J.nbar_in), sa, na, sb, nb, bb0, bb1, fa, fb);
-            if (fa == o0) {
+            belief_regs2<NA, NB, 0, false>(G, as_global(J.nbar_in), sa, sb, bb0, bb1, fa, fb);
+            if (fa == o0 && sa >= 0) {
                 const int at = G.vtile[sa >> 6].b_off + (sa & (kLanes - 1));
 #pragma unroll
                 for (int i = 0; i < NA; ++i) J.thetabar[at + i * kLanes] += bb0[i];
             }
-            if (fb == o1) {
+            if (fb == o1 && sb >= 0) {
                 const int at = G.vtile[sb >> 6].b_off + (sb & (kLanes - 1));
 #pragma unroll
                 for (int j = 0; j < NB; ++j) J.thetabar[at + j * kLanes] += bb1[j];
@@ -1966,12 +2079,16 @@ hipError_t launch_belief(const DevGraph *gs, const WorkItem *items, int n_low, i
     if (n_low + n_mid + n_high <= 0) return hipSuccess;
     dim3 grid(blocks_for(n_low + n_mid, 4) + n_high), block(256);
     const int z = S.swizzle;
+#define BELIEF_CASE(NB)                                                                                       \
+    if (n_high > 0) hipLaunchKernelGGL((k_belief<NB, true>), grid, block, 0, st, gs, items, n_low, n_mid, n_high, z); \
+    else hipLaunchKernelGGL((k_belief<NB, false>), grid, block, 0, st, gs, items, n_low, n_mid, 0, z);
     switch (bucket) {
-    case 2: hipLaunchKernelGGL((k_belief<2>), grid, block, 0, st, gs, items, n_low, n_mid, n_high, z); break;
-    case 4: hipLaunchKernelGGL((k_belief<4>), grid, block, 0, st, gs, items, n_low, n_mid, n_high, z); break;
-    case 8: hipLaunchKernelGGL((k_belief<8>), grid, block, 0, st, gs, items, n_low, n_mid, n_high, z); break;
-    default: hipLaunchKernelGGL((k_belief<16>), grid, block, 0, st, gs, items, n_low, n_mid, n_high, z); break;
+    case 2: BELIEF_CASE(2) break;
+    case 4: BELIEF_CASE(4) break;
+    case 8: BELIEF_CASE(8) break;
+    default: BELIEF_CASE(16) break;
     }
+#undef BELIEF_CASE
     return hipGetLastError();
 }
 

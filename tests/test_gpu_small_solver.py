@@ -43,7 +43,8 @@ SPECS = {
     "g3": lambda: W.potts_grid(33, 3, 6), "g4": lambda: W.potts_grid(23, 4, 7), "g5": lambda: W.potts_grid(17, 5, 8),
     "g6": lambda: W.potts_grid(13, 6, 9), "g7": lambda: W.potts_grid(11, 7, 10), "g8": lambda: W.potts_grid(22, 8, 11),
     # degrees above four and above sixteen, both in one graph
-    "deg12": lambda: W.random_pairwise(12, 300, 900, 4), "deg40": lambda: W.random_pairwise(13, 40, 500, 2, max_degree=40),
+    "deg12": lambda: W.random_pairwise(12, 300, 900, 4),
+    "deg40": lambda: W.random_pairwise(13, 40, 500, 2, max_degree=40),
     "rbm15": lambda: W.rbm(15, 15, seed=14), "rbm17x16": lambda: W.rbm(17, 16, seed=15),
     "rbm64": lambda: W.rbm(64, 64, seed=16), "rbm65x64": lambda: W.rbm(65, 64, seed=17),
     "isolated": lambda: _isolated(W.potts_grid(9, 3, 18)),
