@@ -696,9 +696,17 @@ __device__ __forceinline__ void slot_vars(const GV &G, const FTile &ft, int lane
     vb = a1 >= 0 ? (lane < ft.nact ? a1 + lane : -1) : G.fvar[ft.vb_off + kLanes + lane];
 }
 
+// LSE_T of two entries t0, t1 with larger one M: M + T log(1 + e^{-|t1-t0|/T}).
+// The general form's terms are exp2(0) = 1 for the larger entry and this one's
+// exponential for the other, so the bits agree (a sum of two does not depend
+// on their order), at half the exponentials.
+__device__ __forceinline__ float lse2(float t0, float t1, float M, const TParams &P) {
+    return M + flog2(1.0f + fexp2(-fabsf(t1 - t0) * P.c)) * P.r;
+}
+
 // The update itself: u0[i] = LSE_T,j (p[i][j] + x1[j]) and
 // u1[j] = LSE_T,i (p[i][j] + x0[i]) over na x nb entries.
-template <int NA, int NB, bool MAXP>
+template <int NA, int NB, bool EXACT, bool MAXP>
 __device__ __forceinline__ void pair_update(const float (&p)[NA][NB], const float (&x0)[NA], const float (&x1)[NB],
                                             int na, int nb, const TParams &P, float (&u0)[NA], float (&u1)[NB]) {
     // to slot 0
@@ -715,6 +723,8 @@ __device__ __forceinline__ void pair_update(const float (&p)[NA][NB], const floa
                 }
             if (MAXP) {
                 u0[i] = M;
+            } else if (EXACT && NB == 2) {
+                u0[i] = lse2(t[0], t[1 % NB], M, P);
             } else {
                 float s = 0.0f;
 #pragma unroll
@@ -737,6 +747,8 @@ __device__ __forceinline__ void pair_update(const float (&p)[NA][NB], const floa
                 }
             if (MAXP) {
                 u1[j] = M;
+            } else if (EXACT && NA == 2) {
+                u1[j] = lse2(t[0], t[1 % NA], M, P);
             } else {
                 float s = 0.0f;
 #pragma unroll
@@ -806,7 +818,7 @@ __device__ __forceinline__ void pair_tile(const GV &G, const FTile &ft, int lane
     }
     if (!EARLY) load_table();
     float u0[NA], u1[NB];
-    pair_update<NA, NB, MAXP>(p, x0, x1, na, nb, P, u0, u1);
+    pair_update<NA, NB, EXACT, MAXP>(p, x0, x1, na, nb, P, u0, u1);
     damp_store<NA>(w0, m0, u0, na, P);
     damp_store<NB>(w1, m1, u1, nb, P);
 }
@@ -1320,7 +1332,7 @@ __global__ __launch_bounds__(kPairSolveThreads) void k_solve_pair(const DevGraph
                 x0[s] = B[b0[u] + s * kLanes] - m0[s];
                 x1[s] = B[b1[u] + s * kLanes] - m1[s];
             }
-            pair_update<N, N, MAXP>(p[u], x0, x1, N, N, P, u0, u1);
+            pair_update<N, N, true, MAXP>(p[u], x0, x1, N, N, P, u0, u1);
             damp_store<N>(m + o[u], m0, u0, N, P);
             damp_store<N>(m + o[u] + N * kLanes, m1, u1, N, P);
         }
