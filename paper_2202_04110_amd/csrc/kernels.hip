@@ -409,15 +409,15 @@ __device__ __forceinline__ void belief_low_tile(const GV &G, int t, int lane) {
 // The beliefs of two lane-path variables at once (va with NA states, vb with
 // NB: the fused kernels' square classes) in registers, each with
 // belief_low_tile's additions in its order (theta first, then the edges in
-// order); both gathers are in flight together.  mm:
-// the message panels (MODE as for msg_load); THETA: with the evidence, else
-// the messages' sums alone (the reverse sweep).  fa, fb: the first edges'
-// message addresses (-1: none).
+// order); both gathers are in flight together.  mm: the message panels (MODE
+// as for msg_load).  fa, fb: the first edges' message addresses (-1: none).
 // An idle lane (-1) gathers what the wavefront's first lane does; its
 // result is not used.
-template <int NA, int NB, int MODE, bool THETA, class GV, class PT>
+// TWO: the sums of a second panel set m2 at the same addresses (unpacked, no
+// evidence) come with them in ca, cb.
+template <int NA, int NB, int MODE, bool TWO, class GV, class PT>
 __device__ __forceinline__ void belief_regs2(const GV &G, PT mm, int va, int vb, float (&ba)[NA], float (&bb)[NB],
-                                             int &fa, int &fb) {
+                                             int &fa, int &fb, PT m2, float (&ca)[NA], float (&cb)[NB]) {
     constexpr int KU = 4;
     // (read before the test: under it, the first lane would be an idle one;
     // lane 0 never is)
@@ -427,9 +427,15 @@ __device__ __forceinline__ void belief_regs2(const GV &G, PT mm, int va, int vb,
     const int la = va & (kLanes - 1), lb = vb & (kLanes - 1);
     const VTile ta = G.vtile[va >> 6], tb = G.vtile[vb >> 6];
 #pragma unroll
-    for (int s = 0; s < NA; ++s) ba[s] = THETA ? G.theta[ta.b_off + la + s * kLanes] : 0.0f;
+    for (int s = 0; s < NA; ++s) {
+        ba[s] = G.theta[ta.b_off + la + s * kLanes];
+        if (TWO) ca[s] = 0.0f;
+    }
 #pragma unroll
-    for (int s = 0; s < NB; ++s) bb[s] = THETA ? G.theta[tb.b_off + lb + s * kLanes] : 0.0f;
+    for (int s = 0; s < NB; ++s) {
+        bb[s] = G.theta[tb.b_off + lb + s * kLanes];
+        if (TWO) cb[s] = 0.0f;
+    }
     const int32_t *ea = G.vedge + ta.e_off + la, *eb = G.vedge + tb.e_off + lb;
     const int kmax = max(ta.kmax, tb.kmax);
     fa = fb = -1;
@@ -444,20 +450,36 @@ __device__ __forceinline__ void belief_regs2(const GV &G, PT mm, int va, int vb,
             fa = a[0];
             fb = b[0];
         }
-        float x[KU][NA], y[KU][NB];
+        float x[KU][NA], y[KU][NB], x2[KU][NA], y2[KU][NB];
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
-            msg_load<NA, MODE>(mm + (k0 + u < ta.kmax ? a[u] : G.zero_addr), NA, 0, true, x[u]);
-            msg_load<NB, MODE>(mm + (k0 + u < tb.kmax ? b[u] : G.zero_addr), NB, 0, true, y[u]);
+            const int ra = k0 + u < ta.kmax ? a[u] : G.zero_addr, rb = k0 + u < tb.kmax ? b[u] : G.zero_addr;
+            msg_load<NA, MODE>(mm + ra, NA, 0, true, x[u]);
+            msg_load<NB, MODE>(mm + rb, NB, 0, true, y[u]);
+            if (TWO) {
+                msg_load<NA, 0>(m2 + ra, NA, 0, true, x2[u]);
+                msg_load<NB, 0>(m2 + rb, NB, 0, true, y2[u]);
+            }
         }
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
 #pragma unroll
-            for (int s = 0; s < NA; ++s) ba[s] += x[u][s];
+            for (int s = 0; s < NA; ++s) {
+                ba[s] += x[u][s];
+                if (TWO) ca[s] += x2[u][s];
+            }
 #pragma unroll
-            for (int s = 0; s < NB; ++s) bb[s] += y[u][s];
+            for (int s = 0; s < NB; ++s) {
+                bb[s] += y[u][s];
+                if (TWO) cb[s] += y2[u][s];
+            }
         }
     }
+}
+template <int NA, int NB, int MODE, class GV, class PT>
+__device__ __forceinline__ void belief_regs2(const GV &G, PT mm, int va, int vb, float (&ba)[NA], float (&bb)[NB]) {
+    int fa, fb;
+    belief_regs2<NA, NB, MODE, false>(G, mm, va, vb, ba, bb, fa, fb, mm, ba, bb);
 }
 
 // mid: lane l holds edge l; a wavefront sum (wave_sum: the same bits in
@@ -840,9 +862,9 @@ __device__ __forceinline__ void pair_tile(const GV &G, const FTile &ft, int lane
     float m0[NA], m1[NB], x0[NA], x1[NB];
     if (FUSED) {
         float b0[NA], b1[NB];
-        int va, vb, fa, fb;
+        int va, vb;
         slot_vars(G, ft, lane, t, va, vb);
-        belief_regs2<NA, NB, NA == 2 ? 2 : 0, true>(G, G.m, va, vb, b0, b1, fa, fb);
+        belief_regs2<NA, NB, NA == 2 ? 2 : 0>(G, G.m, va, vb, b0, b1);
         msg_load<NA, 1>(r0, na, 0, true, m0);
         msg_load<NB, 1>(r1, nb, 0, true, m1);
 #pragma unroll
@@ -1622,8 +1644,10 @@ __global__ __launch_bounds__(64) void k_gen_dyn(const DevGraph *__restrict__ gs,
 // and the lane that owns a variable's first edge adds Bbar_{t+1} to thetabar.
 // The first step (nbar_in null) has Bbar from the read-out, and starts A and
 // phibar.  Four launches a step before (beliefs, this, nbar's sums, thetabar);
-// each costs 2.5 us and up whatever the size.  Measured on Potts 64 x 64 with
-// 6 states, 50 iterations, checkpoints every 10: a training step 1470 -> 1256 us.
+// each costs 2.5 us and up whatever the size.  Tables (and phibar) are asked
+// for first, and one pass over the edge addresses serves both sums.  Measured
+// on Potts 64 x 64 with 6 states, 50 iterations, checkpoints every 10: a
+// training step 1470 us with four launches a step, 943 now.
 template <int NA, int NB, bool EXACT, bool FUSED>
 __global__ __launch_bounds__(256) void k_pair_adj(const DevGraph *__restrict__ gs, const WorkItem *__restrict__ items,
                                                   int nitems, TParams P, AdjBufs J) {
@@ -1636,6 +1660,24 @@ __global__ __launch_bounds__(256) void k_pair_adj(const DevGraph *__restrict__ g
     const int na = EXACT ? NA : ft.a;
     const int nb = EXACT ? NB : ft.b;
     const bool first = FUSED && !J.nbar_in;
+    const float *ph = G.phi + ft.phi_off + lane;
+    float *pb = J.phibar + ft.phi_off + lane;
+    // (fused: the tables before the gathers; phibar too, where the registers
+    // leave more than one wavefront per SIMD)
+    constexpr bool EARLY_PB = FUSED && NA <= 6;
+    float p[NA][NB], pb0[NA][NB];
+    if (FUSED) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) p[i][j] = ph[(i * NB + j) * kLanes];
+    }
+    if (EARLY_PB && !first) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) pb0[i][j] = pb[(i * NB + j) * kLanes];
+    }
     int va = 0, vb = 0;  // belief addresses
     if (!FUSED || first) {
         va = G.fvb[ft.vb_off + lane];
@@ -1646,9 +1688,11 @@ __global__ __launch_bounds__(256) void k_pair_adj(const DevGraph *__restrict__ g
     if (FUSED) {
         int sa, sb, fa, fb;
         slot_vars(G, ft, lane, it.t, sa, sb);
-        belief_regs2<NA, NB, NA == 2 ? 2 : 0, true>(G, G.m, sa, sb, x0, x1, fa, fb);
-        if (!first) {
-            belief_regs2<NA, NB, 0, false>(G, as_global(J.nbar_in), sa, sb, bb0, bb1, fa, fb);
+        if (first) {
+            belief_regs2<NA, NB, NA == 2 ? 2 : 0>(G, G.m, sa, sb, x0, x1);
+        } else {
+            belief_regs2<NA, NB, NA == 2 ? 2 : 0, true>(G, (gptr<const float>)G.m, sa, sb, x0, x1, fa, fb,
+                                                        as_global(J.nbar_in), bb0, bb1);
             if (fa == o0 && sa >= 0) {
                 const int at = G.vtile[sa >> 6].b_off + (sa & (kLanes - 1));
 #pragma unroll
@@ -1684,13 +1728,13 @@ __global__ __launch_bounds__(256) void k_pair_adj(const DevGraph *__restrict__ g
 #pragma unroll
     for (int j = 0; j < NB; ++j)
         if (j < nb) x1[j] = x1[j] - m1[j];
-    const float *ph = G.phi + ft.phi_off + lane;
-    float p[NA][NB];
+    if (!FUSED) {
 #pragma unroll
-    for (int i = 0; i < NA; ++i)
+        for (int i = 0; i < NA; ++i)
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
-            if (i < na && j < nb) p[i][j] = ph[(i * nb + j) * kLanes];
+            for (int j = 0; j < NB; ++j)
+                if (i < na && j < nb) p[i][j] = ph[(i * nb + j) * kLanes];
+    }
     // forward: u (LSE per row / column), exactly as in the forward kernel
     float u0[NA], u1[NB];
 #pragma unroll
@@ -1779,7 +1823,6 @@ __global__ __launch_bounds__(256) void k_pair_adj(const DevGraph *__restrict__ g
     for (int i = 0; i < NA; ++i) rs0[i] = 0.0f;
 #pragma unroll
     for (int j = 0; j < NB; ++j) rs1[j] = 0.0f;
-    float *pb = J.phibar + ft.phi_off + lane;
 #pragma unroll
     for (int i = 0; i < NA; ++i)
 #pragma unroll
@@ -1788,7 +1831,8 @@ __global__ __launch_bounds__(256) void k_pair_adj(const DevGraph *__restrict__ g
                 const float pa = fexp2((p[i][j] + x1[j] - u0[i]) * P.c);
                 const float pbv = fexp2((p[i][j] + x0[i] - u1[j]) * P.c);
                 const float sb = gu0[i] * pa + gu1[j] * pbv;
-                pb[(i * nb + j) * kLanes] = (first ? 0.0f : pb[(i * nb + j) * kLanes]) + sb;
+                pb[(i * nb + j) * kLanes] =
+                    (first ? 0.0f : EARLY_PB ? pb0[i][j] : pb[(i * nb + j) * kLanes]) + sb;
                 rs0[i] += sb;
                 rs1[j] += sb;
             }
@@ -1914,19 +1958,57 @@ __global__ __launch_bounds__(256) void k_readout_adj(const DevGraph *__restrict_
     const int b0 = G.vtile[w].b_off + lane;
     const float *b = G.B + b0;
     const float *g = gq + G.vs_off[v];
+    // the first eight states in registers, as in readout_tile
+    constexpr int KR = 8;
+    float x[KR], gx[KR];
+#pragma unroll
+    for (int s = 0; s < KR; ++s) {
+        x[s] = b[min(s, n - 1) * kLanes];
+        gx[s] = g[min(s, n - 1)];
+    }
     float M = -INFINITY, tot = 0.0f;
-    for (int s = 0; s < n; ++s) {
+#pragma unroll
+    for (int s = 0; s < KR; ++s)
+        if (s < n) {
+            M = fmaxf(M, x[s]);
+            tot += gx[s];
+        }
+    for (int s = KR; s < n; ++s) {
         M = fmaxf(M, b[s * kLanes]);
         tot += g[s];
     }
     float z = 0.0f;
-    for (int s = 0; s < n; ++s) z += fexp2((b[s * kLanes] - M) * P.c);
+#pragma unroll
+    for (int s = 0; s < KR; ++s)
+        if (s < n) z += fexp2((x[s] - M) * P.c);
+    for (int s = KR; s < n; ++s) z += fexp2((b[s * kLanes] - M) * P.c);
     const float iz = 1.0f / z;
-    for (int s = 0; s < n; ++s) {
-        const float pr = fexp2((b[s * kLanes] - M) * P.c) * iz;
-        const float x = g[s] - pr * tot;
-        bbar[b0 + s * kLanes] = x;
-        thetabar[b0 + s * kLanes] = x;
+    auto put = [&](int s, float bv, float gv) {
+        const float pr = fexp2((bv - M) * P.c) * iz;
+        const float r = gv - pr * tot;
+        bbar[b0 + s * kLanes] = r;
+        thetabar[b0 + s * kLanes] = r;
+    };
+#pragma unroll
+    for (int s = 0; s < KR; ++s)
+        if (s < n) put(s, x[s], gx[s]);
+    for (int s = KR; s < n; ++s) put(s, b[s * kLanes], g[s]);
+}
+
+// Copies n values from a row of stride SS to one of stride DS, kCopyUnroll
+// loads in flight at a time (a load past the end repeats the last).  One value
+// at a time, each behind its own wait, Potts 64 x 64's 36-entry tables took
+// 17 us to write out and 10 to read in.
+constexpr int kCopyUnroll = 8;
+template <int SS, int DS, class SP, class DP>
+__device__ __forceinline__ void copy_row(SP src, DP dst, int n) {
+    for (int s0 = 0; s0 < n; s0 += kCopyUnroll) {
+        float x[kCopyUnroll];
+#pragma unroll
+        for (int u = 0; u < kCopyUnroll; ++u) x[u] = src[min(s0 + u, n - 1) * SS];
+#pragma unroll
+        for (int u = 0; u < kCopyUnroll; ++u)
+            if (s0 + u < n) dst[(s0 + u) * DS] = x[u];
     }
 }
 
@@ -1946,7 +2028,7 @@ __global__ void k_logpot_out(const DevGraph *__restrict__ gs, const float *__res
     if (base < 0) return;
     const int64_t o = G.lp_off[f];
     const int n = (int)(G.lp_off[f + 1] - o);
-    for (int c = 0; c < n; ++c) out[o + c] = panel[base + c * kLanes];
+    copy_row<kLanes, 1>(panel + base, out + o, n);
 }
 
 __global__ void k_evidence_out(const DevGraph *__restrict__ gs, const float *__restrict__ panel,
@@ -1956,7 +2038,7 @@ __global__ void k_evidence_out(const DevGraph *__restrict__ gs, const float *__r
     if (v >= G.V) return;
     const float *row = panel + G.vtile[v / kLanes].b_off + (v % kLanes);
     const int64_t o = G.vs_off[v];
-    for (int s = 0; s < G.vn[v]; ++s) out[o + s] = row[s * kLanes];
+    copy_row<kLanes, 1>(row, out + o, G.vn[v]);
 }
 
 // --------------------------------------------------------------------------
@@ -1975,17 +2057,26 @@ __device__ __forceinline__ void readout_tile(const GV &G, int w, const TParams &
     const VTile vt = G.vtile[w];
     const int n = G.vn[v];
     const float *b = G.B + vt.b_off + lane;
+    // the first eight states stay in registers (all of them, mostly); a load
+    // past the last repeats it
+    constexpr int KR = 8;
+    float x[KR];
+#pragma unroll
+    for (int s = 0; s < KR; ++s) x[s] = b[min(s, n - 1) * kLanes];
     float M = -INFINITY;
     int best = 0;
     bool finite = true;
-    for (int s = 0; s < n; ++s) {
-        const float x = b[s * kLanes];
-        finite = finite && isfinite(x);
-        if (x > M) {
-            M = x;
+    auto take = [&](int s, float v) {
+        finite = finite && isfinite(v);
+        if (v > M) {
+            M = v;
             best = s;
         }
-    }
+    };
+#pragma unroll
+    for (int s = 0; s < KR; ++s)
+        if (s < n) take(s, x[s]);
+    for (int s = KR; s < n; ++s) take(s, b[s * kLanes]);
     if (!finite) {
         G.flag[0] = 1;
         if (flag_host) flag_host[0] = 1;
@@ -1998,12 +2089,18 @@ __device__ __forceinline__ void readout_tile(const GV &G, int w, const TParams &
                 z = M;
             } else {
                 float s = 0.0f;
-                for (int t = 0; t < n; ++t) s += fexp2((b[t * kLanes] - M) * P.c);
+#pragma unroll
+                for (int t = 0; t < KR; ++t)
+                    if (t < n) s += fexp2((x[t] - M) * P.c);
+                for (int t = KR; t < n; ++t) s += fexp2((b[t * kLanes] - M) * P.c);
                 z = M + flog2(s) * P.r;
             }
         }
         float *q = qout + G.vs_off[v];
-        for (int s = 0; s < n; ++s) q[s] = b[s * kLanes] - z;
+#pragma unroll
+        for (int s = 0; s < KR; ++s)
+            if (s < n) q[s] = x[s] - z;
+        for (int s = KR; s < n; ++s) q[s] = b[s * kLanes] - z;
     }
 }
 
@@ -2034,7 +2131,13 @@ __global__ void k_msgs_out(const DevGraph *__restrict__ gs, float *__restrict__ 
     const float *row = G.m + G.edge_maddr[e];
     const int64_t o = G.es_off[e];
     const int n = (int)(G.es_off[e + 1] - o);
-    for (int s = 0; s < n; ++s) out[o + s] = msg_state(row, n, s);
+    if (n == 2) {
+        const float d = row[0];
+        out[o] = pk_m0(d);
+        out[o + 1] = pk_m1(d);
+        return;
+    }
+    copy_row<kLanes, 1>(row, out + o, n);
 }
 
 __global__ void k_msgs_in(const DevGraph *__restrict__ gs, const float *__restrict__ in) {
@@ -2049,7 +2152,7 @@ __global__ void k_msgs_in(const DevGraph *__restrict__ gs, const float *__restri
         row[0] = (v1 - mx) - (v0 - mx);
         return;
     }
-    for (int s = 0; s < n; ++s) row[s * kLanes] = in[o + s];
+    copy_row<1, kLanes>(in + o, row, n);
 }
 
 __global__ void k_evidence_in(const DevGraph *__restrict__ gs, const float *__restrict__ in) {
@@ -2058,7 +2161,7 @@ __global__ void k_evidence_in(const DevGraph *__restrict__ gs, const float *__re
     if (v >= G.V) return;
     float *row = G.theta + G.vtile[v / kLanes].b_off + (v % kLanes);
     const int64_t o = G.vs_off[v];
-    for (int s = 0; s < G.vn[v]; ++s) row[s * kLanes] = in[o + s];
+    copy_row<1, kLanes>(in + o, row, G.vn[v]);
 }
 
 // Residual of an iteration: the largest |m - mprev| over the edge-state
@@ -2150,7 +2253,19 @@ __global__ void k_evidence_perturb(const DevGraph *__restrict__ views, const flo
     if (v >= G.V) return;
     const int64_t addr = G.vtile[v / kLanes].b_off + (v % kLanes);
     const float *nz = noise + (int64_t)s * VS + G.vs_off[v];
-    for (int t = 0; t < G.vn[v]; ++t) G.theta[addr + t * kLanes] = base[addr + t * kLanes] + nz[t];
+    const int n = G.vn[v];
+    for (int s0 = 0; s0 < n; s0 += kCopyUnroll) {
+        float x[kCopyUnroll], y[kCopyUnroll];
+#pragma unroll
+        for (int u = 0; u < kCopyUnroll; ++u) {
+            const int t = min(s0 + u, n - 1);
+            x[u] = base[addr + t * kLanes];
+            y[u] = nz[t];
+        }
+#pragma unroll
+        for (int u = 0; u < kCopyUnroll; ++u)
+            if (s0 + u < n) G.theta[addr + (s0 + u) * kLanes] = x[u] + y[u];
+    }
 }
 
 __global__ void k_logpot_in(const DevGraph *__restrict__ gs, const float *__restrict__ in) {
@@ -2161,7 +2276,7 @@ __global__ void k_logpot_in(const DevGraph *__restrict__ gs, const float *__rest
     if (base < 0) return;
     const int64_t o = G.lp_off[f];
     const int n = (int)(G.lp_off[f + 1] - o);
-    for (int c = 0; c < n; ++c) G.phi[base + c * kLanes] = in[o + c];
+    copy_row<1, kLanes>(in + o, G.phi + base, n);
 }
 
 inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }

@@ -752,7 +752,13 @@ int adjoint_backward(lbp_graph *g, const float *grad_q, float *grad_logpot, floa
     // Fused form: one launch per recomputed iteration and per reverse step.  A
     // segment's first iterate is its checkpoint itself, which leaves the first
     // iterate buffer to the second nbar.
-    const bool fused = g->fusable && J.iters > 0;
+    // (Eight states, past a wavefront per compute unit: the gathers of 256
+    // messages a lane cost more than the launches. Start / fused, 20 iterations:
+    // 80 x 80 742 / 644 us, 110 x 110 789 / 799, 160 x 160 over 30 iterations
+    // 1264 / 1307; 250 x 250 with seven states 1159 / 1106.)
+    bool fused = g->fusable && J.iters > 0;
+    for (const Launch &L : g->fl)
+        if (L.a >= 8 && L.n > 256) fused = false;
     float *nbar[2] = {J.nbar, J.seg};
     int cur = 0;  // the nbar written last
     AdjBufs B{J.A, J.nbar, J.Bbar, J.phibar, nullptr, J.thetabar};
