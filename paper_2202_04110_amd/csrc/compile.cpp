@@ -422,6 +422,19 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
     // against the number of blocks, a comparison sort otherwise: same order)
     const int64_t nblk = (V + kLanes - 1) / kLanes;
     std::vector<int32_t> blk_start, sorted;
+    // dense three-way classes with 2..4 states in every slot run in registers
+    auto tri_class = [&](size_t c) {
+        const std::vector<int32_t> &ns = std::get<4>(class_key[c]);
+        return std::get<0>(class_key[c]) == TK_GEN && std::get<3>(class_key[c]) < 0 && ns.size() == 3 &&
+               ns[0] == ns[1] && ns[1] == ns[2] && ns[0] >= 2 && ns[0] <= 4;
+    };
+    // the offsets at which a pairwise or three-way factor joins its variables
+    auto offsets = [&](int32_t f) {
+        const int64_t e0 = d->factor_edge_off[f];
+        const int64_t d1 = (int64_t)d->edge_var[e0 + 1] - d->edge_var[e0];
+        if (d->factor_edge_off[f + 1] - e0 == 2) return std::make_pair(d1, (int64_t)0);
+        return std::make_pair(d1, (int64_t)d->edge_var[e0 + 2] - d->edge_var[e0]);
+    };
     for (size_t c = 0; c < class_key.size(); ++c) {
         if (std::get<0>(class_key[c]) == TK_LOGW) continue;
         std::vector<int32_t> &fl = class_facs[c];
@@ -452,7 +465,8 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
                 i = j;
             }
         }
-        if (std::get<0>(class_key[c]) != TK_PAIR) continue;
+        const bool pair = std::get<0>(class_key[c]) == TK_PAIR;
+        if (!pair && !tri_class(c)) continue;
         // pairwise factors that all join two block-path variables (a dense
         // bipartite layer): ordered by the 16-variable block of the second
         // variable, then the first, so a tile holds 4 x 16 factors and a run
@@ -462,7 +476,7 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
         {
             auto var0 = [&](int32_t f) { return (int64_t)d->edge_var[d->factor_edge_off[f]]; };
             auto var1 = [&](int32_t f) { return (int64_t)d->edge_var[d->factor_edge_off[f] + 1]; };
-            bool layer = !fl.empty();
+            bool layer = pair && !fl.empty();
             for (size_t i = 0; i < fl.size() && layer; ++i)
                 layer = adj_off[var0(fl[i]) + 1] - adj_off[var0(fl[i])] > kMidDegMax &&
                         adj_off[var1(fl[i]) + 1] - adj_off[var1(fl[i])] > kMidDegMax;
@@ -482,23 +496,19 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
                 continue;
             }
         }
-        // pairwise: inside a block whose factors join their two variables at
-        // no more than four distinct offsets (a grid: horizontal and vertical
-        // neighbours), factors with the same offset together, each group in
-        // its existing order; other blocks keep their order
-        auto delta = [&](int32_t f) {
-            const int64_t e0 = d->factor_edge_off[f];
-            return (int64_t)d->edge_var[e0 + 1] - d->edge_var[e0];
-        };
+        // inside a block whose factors join their variables at no more than
+        // four distinct offsets (a grid: horizontal and vertical neighbours),
+        // factors with the same offset together, each group in its existing
+        // order; other blocks keep their order
         std::vector<int32_t> part;
         for (size_t i = 0; i < fl.size();) {
             size_t j = i;
             while (j < fl.size() && key(fl[j]) == key(fl[i])) ++j;
-            int64_t seen[4];
+            std::pair<int64_t, int64_t> seen[4];
             int nseen = 0;
             bool few = true;
             for (size_t k = i; k < j && few; ++k) {
-                const int64_t dk = delta(fl[k]);
+                const auto dk = offsets(fl[k]);
                 int s = 0;
                 while (s < nseen && seen[s] != dk) ++s;
                 if (s == nseen) {
@@ -511,12 +521,29 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
                 part.clear();
                 for (int s = 0; s < nseen; ++s)
                     for (size_t k = i; k < j; ++k)
-                        if (delta(fl[k]) == seen[s]) part.push_back(fl[k]);
+                        if (offsets(fl[k]) == seen[s]) part.push_back(fl[k]);
                 std::copy(part.begin(), part.end(), fl.begin() + (int64_t)i);
             }
             i = j;
         }
     }
+    // Pairwise and register three-way tiles take 64 consecutive factors, but a
+    // tile whose factors so far form one (block, variable offsets) group closes
+    // early where that group ends, once 48 lanes are filled: a grid's tiles then
+    // each hold one run of horizontal or vertical factors, whose slot variables
+    // are consecutive lanes.  Graphs whose offsets scatter keep full tiles.
+    auto run_length = [&](const std::vector<int32_t> &facs, size_t i0) {
+        auto group = [&](size_t i) {
+            return std::make_pair(d->edge_var[d->factor_edge_off[facs[i]]] / kLanes, offsets(facs[i]));
+        };
+        size_t len = std::min<size_t>(kLanes, facs.size() - i0);
+        if (len > 48 && group(i0) == group(i0 + 47)) {
+            size_t l = 1;
+            while (l < len && group(i0 + l) == group(i0)) ++l;
+            if (l >= 48) len = l;  // one run up to lane l (else the run broke early: a full tile)
+        }
+        return len;
+    };
     for (size_t c = 0; c < class_key.size(); ++c) {
         const int32_t kind = std::get<0>(class_key[c]);
         const std::vector<int32_t> &facs = class_facs[c];
@@ -528,24 +555,8 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
             const int32_t na = std::get<1>(class_key[c]), nb = std::get<2>(class_key[c]);
             grp.a = na;
             grp.b = nb;
-            // Tiles take 64 consecutive factors, but a tile whose factors so
-            // far form one (block, variable offset) group closes early where
-            // that group ends, once 48 lanes are filled: a grid's tiles then
-            // each hold one run of horizontal or vertical factors, whose slot
-            // variables are consecutive lanes.  Graphs whose offsets scatter
-            // keep full tiles.
-            auto group = [&](size_t i) {
-                const int64_t e0 = d->factor_edge_off[facs[i]];
-                return std::make_pair((int64_t)d->edge_var[e0] / kLanes,
-                                      (int64_t)d->edge_var[e0 + 1] - d->edge_var[e0]);
-            };
             for (size_t i0 = 0, len = 0; i0 < facs.size(); i0 += len) {
-                len = std::min<size_t>(kLanes, facs.size() - i0);
-                if (len > 48 && group(i0) == group(i0 + 47)) {
-                    size_t l = 1;
-                    while (l < len && group(i0 + l) == group(i0)) ++l;
-                    if (l >= 48) len = l;  // one run up to lane l (else the run broke early: a full tile)
-                }
+                len = run_length(facs, i0);
                 FTile ft{};
                 ft.kind = TK_PAIR;
                 ft.a = na;
@@ -659,13 +670,14 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
             L->gcls.push_back(gc);
             // launch groups: dense three-way classes with 2..4 states in every
             // slot run in registers (code -N); the others by LDS need
-            const bool tri = t < 0 && k == 3 && ns[0] == ns[1] && ns[1] == ns[2] && ns[0] >= 2 && ns[0] <= 4;
+            const bool tri = tri_class(c);
             grp.a = tri ? -ns[0] : gen_lds_code(gc.ncfg * gc.arity, gc.nrows);
-            for (size_t i0 = 0; i0 < facs.size(); i0 += kLanes) {
+            for (size_t i0 = 0, len = 0; i0 < facs.size(); i0 += len) {
+                len = tri ? run_length(facs, i0) : std::min<size_t>(kLanes, facs.size() - i0);
                 FTile ft{};
                 ft.kind = TK_GEN;
                 ft.a = gidx;
-                ft.nact = (int32_t)std::min<size_t>(kLanes, facs.size() - i0);
+                ft.nact = (int32_t)len;
                 ft.m_off = (int32_t)M;
                 ft.phi_off = (int32_t)P;
                 ft.vb_off = (int32_t)L->fvb.size();
@@ -875,6 +887,9 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
     L->fusable = L->hvar.empty() && !L->fgroups.empty();
     for (const FGroup &fg : L->fgroups)
         if (fg.kind != TK_PAIR || fg.a != fg.b) L->fusable = false;
+    L->tri_fusable = L->hvar.empty() && !L->fgroups.empty();
+    for (const FGroup &fg : L->fgroups)
+        if (fg.kind != TK_GEN || fg.a >= 0) L->tri_fusable = false;
 
     // -------------------------------------------------------------- values
     if (!fill) {

@@ -97,9 +97,11 @@ hipError_t launch_logical(const DevGraph *gs, const WorkItem *items, int n, bool
 // Generic classes.  lds_code -N: dense three-way classes with N (2..4)
 // states per slot, in registers; 0: the kernel with LDS for the largest
 // class; otherwise gen_lds_code(rows bytes, summed slot states) of the
-// classes in the launch, which sizes its dynamic LDS.
+// classes in the launch, which sizes its dynamic LDS.  fused (three-way
+// classes, every variable on the lane path): one whole iteration, reading G.m
+// and writing G.mo.
 hipError_t launch_gen(const DevGraph *gs, const WorkItem *items, int n, bool maxp, const TParams &P, int lds_code,
-                      hipStream_t st);
+                      hipStream_t st, bool fused = false);
 // Read-out of a single graph (gs[0]).
 // `iters` iterations of one small graph in a single workgroup holding the
 // arrays of plan.lds_mask in LDS (plan.lds_words words, which must include

@@ -482,6 +482,43 @@ __device__ __forceinline__ void belief_regs2(const GV &G, PT mm, int va, int vb,
     belief_regs2<NA, NB, MODE, false>(G, mm, va, vb, ba, bb, fa, fb, mm, ba, bb);
 }
 
+// The beliefs of three lane-path variables of N states, as belief_regs2.
+template <int N, int MODE, class GV>
+__device__ __forceinline__ void belief_regs3(const GV &G, const int (&v)[3], float (&b)[3][N]) {
+    constexpr int KU = N <= 3 ? 6 : 4;  // (grid triples give a variable six edges)
+    VTile t[3];
+    int kmax = 0;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        t[j] = G.vtile[v[j] >> 6];
+        kmax = max(kmax, t[j].kmax);
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int s = 0; s < N; ++s) b[j][s] = G.theta[t[j].b_off + (v[j] & (kLanes - 1)) + s * kLanes];
+    for (int k0 = 0; k0 < kmax; k0 += KU) {
+        int a[3][KU];
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int u = 0; u < KU; ++u)
+                a[j][u] = G.vedge[t[j].e_off + min(k0 + u, t[j].kmax - 1) * kLanes + (v[j] & (kLanes - 1))];
+        float x[3][KU][N];
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int u = 0; u < KU; ++u)
+                msg_load<N, MODE>(G.m + (k0 + u < t[j].kmax ? a[j][u] : G.zero_addr), N, 0, true, x[j][u]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int u = 0; u < KU; ++u)
+#pragma unroll
+                for (int s = 0; s < N; ++s) b[j][s] += x[j][u][s];
+    }
+}
+
 // mid: lane l holds edge l; a wavefront sum (wave_sum: the same bits in
 // every lane) adds up each state.
 // MU two-state variables a wavefront, their loads in flight together (items
@@ -1526,17 +1563,34 @@ __device__ __forceinline__ void gen_tile(const GV &G, const FTile &ft, int lane,
 // incoming terms and scores in registers.  The generic class layout (rows of
 // slot j at j*N), so the reverse sweep's generic kernel serves these tiles.
 // u_j[s] = LSE_T{score(c) : c_j = s} - n_j[s], score = phi + n_0 + n_1 + n_2.
-template <int N, bool MAXP, class GV>
+// FUSED: the slots' beliefs are formed here from the messages being read
+// (belief_regs3), and the messages written to G.mo, another buffer: one launch
+// an iteration instead of two.  Bound by launch and latency while the graph
+// sits in L2 (tri_fused_wins draws the line).  Per iteration on a 64 x 64 grid
+// of three states at T = 1 6.5 / 4.9 us, on 256 x 256 10.5 / 9.3 (with tiles
+// grouped by variable offsets, as pairwise ones, in both).
+template <int N, bool MAXP, bool FUSED, class GV>
 __device__ __forceinline__ void tri_tile(const GV &G, const FTile &ft, int lane, const TParams &P) {
     const float *mrow = G.m + ft.m_off + lane;
     float m[3][N], x[3][N];
+    if (FUSED) {
+        int v[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {  // (an idle lane works on lane 0's variables; its result is not used)
+            v[j] = G.fvar[ft.vb_off + j * kLanes + lane];
+            const int v0 = __builtin_amdgcn_readfirstlane(v[j]);
+            v[j] = v[j] < 0 ? v0 : v[j];
+        }
+        belief_regs3<N, N == 2 ? 2 : 0>(G, v, x);
+    }
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        const int vb = G.fvb[ft.vb_off + j * kLanes + lane];
+        int vb = 0;
+        if (!FUSED) vb = G.fvb[ft.vb_off + j * kLanes + lane];
 #pragma unroll
         for (int s = 0; s < N; ++s) {
             m[j][s] = msg_state(mrow + j * N * kLanes, N, s);
-            x[j][s] = G.B[vb + s * kLanes] - m[j][s];
+            x[j][s] = (FUSED ? x[j][s] : G.B[vb + s * kLanes]) - m[j][s];
         }
     }
     const float *ph = G.phi + ft.phi_off + lane;
@@ -1579,14 +1633,14 @@ __device__ __forceinline__ void tri_tile(const GV &G, const FTile &ft, int lane,
     for (int j = 0; j < 3; ++j) damp_store<N>(wrow + j * N * kLanes, m[j], u[j], N, P);
 }
 
-template <int N, bool MAXP>
+template <int N, bool MAXP, bool FUSED>
 __global__ __launch_bounds__(256) void k_tri(const DevGraph *__restrict__ gs, const WorkItem *__restrict__ items,
                                              int nitems, TParams P) {
     const int w = wave_index(4);
     if (w >= nitems) return;
     const WorkItem it = items[w];
     const GGraph G = glob(gs[it.g]);
-    tri_tile<N, MAXP>(G, G.ftile[it.t], lane_id(), P);
+    tri_tile<N, MAXP, FUSED>(G, G.ftile[it.t], lane_id(), P);
 }
 
 // Any class within the kernel limits: LDS for the largest (80 KB), which
@@ -2446,20 +2500,28 @@ hipError_t launch_logical(const DevGraph *gs, const WorkItem *items, int n, bool
 }
 
 hipError_t launch_gen(const DevGraph *gs, const WorkItem *items, int n, bool maxp, const TParams &P, int lds_code,
-                      hipStream_t st) {
+                      hipStream_t st, bool fused) {
     if (n <= 0) return hipSuccess;
+    if (fused && lds_code >= 0) return hipErrorInvalidValue;
     if (lds_code < 0) {  // dense three-way, -N states per slot
         dim3 grid(blocks_for(n, 4)), block(256);
         switch (-lds_code) {
-#define TRI_CASE(K)                                                                                 \
-    case K:                                                                                         \
-        if (maxp) hipLaunchKernelGGL((k_tri<K, true>), grid, block, 0, st, gs, items, n, P);     \
-        else hipLaunchKernelGGL((k_tri<K, false>), grid, block, 0, st, gs, items, n, P);         \
+#define TRI_LAUNCH(K, FUSED)                                                                        \
+    if (maxp) hipLaunchKernelGGL((k_tri<K, true, FUSED>), grid, block, 0, st, gs, items, n, P);     \
+    else hipLaunchKernelGGL((k_tri<K, false, FUSED>), grid, block, 0, st, gs, items, n, P);
+#define TRI_CASE(K)                 \
+    case K:                         \
+        if (fused) {                \
+            TRI_LAUNCH(K, true)     \
+        } else {                    \
+            TRI_LAUNCH(K, false)    \
+        }                           \
         break;
             TRI_CASE(2)
             TRI_CASE(3)
             TRI_CASE(4)
 #undef TRI_CASE
+#undef TRI_LAUNCH
         default: return hipErrorInvalidValue;
         }
     } else if (lds_code == 0) {

@@ -219,7 +219,9 @@ hipError_t launch_loop(const DevGraph *gs, const DevGraph *fused, const std::vec
         for (; it + 1 < iters && e == hipSuccess; it += 2)
             for (int h = 0; h < 2 && e == hipSuccess; ++h)
                 for (const Launch &L : fl) {
-                    e = launch_pair(fused + h * fused_stride, L.items, L.n, L.a, L.b, maxp, P, L.fshape, st, true);
+                    const DevGraph *view = fused + h * fused_stride;
+                    e = L.kind == TK_PAIR ? launch_pair(view, L.items, L.n, L.a, L.b, maxp, P, L.fshape, st, true)
+                                          : launch_gen(view, L.items, L.n, maxp, P, L.a, st, true);
                     if (e != hipSuccess) break;
                 }
     for (; it < iters && e == hipSuccess; ++it) e = launch_iteration(gs, vl, fl, P, maxp, st);
@@ -296,7 +298,7 @@ struct GraphPieces {
     bool fused;
     LaunchLists ll;
 
-    GraphPieces(const HostLayout &L, bool with_fused) : fused(with_fused && L.fusable) {
+    GraphPieces(const HostLayout &L, bool with_fused) : fused(with_fused && (L.fusable || L.tri_fusable)) {
         auto add = [&](const void *src, size_t bytes) {
             p.push_back(Piece{src, bytes, total});
             total += align256(std::max<size_t>(bytes, 4));
@@ -471,9 +473,14 @@ int graph_create(lbp_ctx *ctx, const HostLayout &L, bool with_fused, char *mem, 
             fv[1] = g->host;
             fv[1].m = m2;
             fv[1].mo = g->host.m;
-            g->fused = (DevGraph *)ptr(gp.fdg);
-            g->m2 = m2;
-            if (e == hipSuccess) e = hipMemcpyAsync(g->fused, fv, sizeof(fv), hipMemcpyHostToDevice, st);
+            DevGraph *views = (DevGraph *)ptr(gp.fdg);
+            if (L.fusable) {
+                g->fused = views;
+                g->m2 = m2;
+            } else {
+                g->tri = views;
+            }
+            if (e == hipSuccess) e = hipMemcpyAsync(views, fv, sizeof(fv), hipMemcpyHostToDevice, st);
         }
         describe_lists(gp.ll, (char *)ptr(gp.items), &g->vl, &g->fl);
         // the host image and the descriptors must outlive the copies (the
@@ -590,6 +597,22 @@ static bool pair_solve_wins(const PairSolve &S, bool maxp) {
     return cycles < 340 * (S.nmid ? 45 : 29 + 4 * (n - 2));
 }
 
+// Fused iterations of three-way graphs gather each variable's messages once
+// per factor that touches it, which pays while they sit in L2 and the second
+// launch is a good part of an iteration.  Two-phase / fused, us per iteration
+// at T = 1 and T = 0 (tiles in brackets): three states, 256 x 256 (2080)
+// 10.3 / 9.3 and 8.9 / 8.1, 300 x 300 (2900) 13.0 / 12.1 and 11.0 / 11.1,
+// 350 x 350 (3900) 15.8 / 15.1 and 13.7 / 14.1, 400 x 400 17.6 / 18.3; four
+// states, 256 x 256 16.3 / 15.5 and 13.5 / 12.5, 200 x 200 (1290) 9.8 / 10.1 at
+// T = 0; two states, 500 x 500 (8050) 12.9 / 12.7 and 12.4 / 12.0.
+static bool tri_fused_wins(const std::vector<Launch> &fl, bool maxp) {
+    for (const Launch &L : fl) {
+        const int32_t most = L.a == -2 ? 8192 : L.a == -3 ? (maxp ? 2500 : 4000) : (maxp ? 1000 : 2500);
+        if (L.n > most) return false;
+    }
+    return true;
+}
+
 hipError_t run_graph(lbp_graph *g, int32_t iters, float d, float T) {
     if (g->small.n && iters >= 2 && pair_solve_wins(g->small, T == 0.0f)) {
         const hipError_t e =
@@ -598,7 +621,8 @@ hipError_t run_graph(lbp_graph *g, int32_t iters, float d, float T) {
         (void)hipGetLastError();  // refused (LDS size): launched iterations from here on
         g->small.n = 0;
     }
-    return run_loop(g->ctx, g->loops, g->dgraph, g->use_fused ? g->fused : nullptr, g->vl, g->fl, iters, d, T);
+    const DevGraph *tri = g->tri && tri_fused_wins(g->fl, T == 0.0f) ? g->tri : nullptr;
+    return run_loop(g->ctx, g->loops, g->dgraph, g->use_fused ? g->fused : tri, g->vl, g->fl, iters, d, T);
 }
 
 void graph_destroy(lbp_graph *g) {

@@ -118,6 +118,7 @@ struct lbp_graph {
     lbp::DevGraph *dgraph = nullptr;  // device copy
     lbp::DevGraph *fused = nullptr;   // device [2]: fused views over the two message buffers, or null
     float *m2 = nullptr;              // the second message buffer of a fusable graph (device), or null
+    lbp::DevGraph *tri = nullptr;     // device [2]: the same of a graph of three-way factors, or null
     bool use_fused = false;           // lbp_run_bp runs fused iterations (chosen by the autotuner)
     bool resident_ok = false;         // small enough for the resident solver (plan below)
     bool use_resident = false;        // lbp_run_bp runs the resident solver (chosen by the autotuner)
