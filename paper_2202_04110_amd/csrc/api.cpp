@@ -268,22 +268,22 @@ int lbp_run_bp_until(lbp_graph *g, int32_t max_iters, float damping, float tempe
             return fail(LBP_E_OOM, "convergence workspace");
         }
     }
-    float *mprev = (float *)g->conv, *partial = (float *)(g->conv + mb), *res = partial + nb;
+    if (!g->residual && hipHostMalloc((void **)&g->residual, 64, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        g->residual = nullptr;
+        return fail(LBP_E_OOM, "convergence workspace");
+    }
+    float *mprev = (float *)g->conv, *partial = (float *)(g->conv + mb);
     ++g->version;
     g->last_T = temperature;
     int32_t done = 0;
     float r = 0.0f;
     while (done < max_iters) {
         const int32_t c = std::min(check_every, max_iters - done);
-        hipError_t e = hipSuccess;
-        if (c > 1)
-            e = run_graph(g, c - 1, damping, temperature);
-        if (e == hipSuccess) e = hipMemcpyAsync(mprev, g->host.m, sizeof(float) * g->M, hipMemcpyDeviceToDevice, st);
-        if (e == hipSuccess) e = run_loop(g->ctx, g->loops, g->dgraph, nullptr, g->vl, g->fl, 1, damping, temperature);
-        if (e == hipSuccess) e = launch_residual(g->dgraph, (int)g->E, mprev, partial, res, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(&r, res, sizeof(float), hipMemcpyDeviceToHost, st);
+        hipError_t e = run_graph_residual(g, c, damping, temperature, mprev, partial, g->residual);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return hip_error(e, "iteration launch");
+        r = *(volatile float *)g->residual;
         done += c;
         if (r < tol) break;
     }

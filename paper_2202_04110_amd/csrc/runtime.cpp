@@ -210,6 +210,17 @@ hipError_t launch_iteration(const DevGraph *gs, const std::vector<Launch> &vl, c
     return e;
 }
 
+hipError_t launch_fused(const DevGraph *view, const std::vector<Launch> &fl, const TParams &P, bool maxp,
+                        hipStream_t st) {
+    hipError_t e = hipSuccess;
+    for (const Launch &L : fl) {
+        e = L.kind == TK_PAIR ? launch_pair(view, L.items, L.n, L.a, L.b, maxp, P, L.fshape, st, true)
+                              : launch_gen(view, L.items, L.n, maxp, P, L.a, st, true);
+        if (e != hipSuccess) break;
+    }
+    return e;
+}
+
 hipError_t launch_loop(const DevGraph *gs, const DevGraph *fused, const std::vector<Launch> &vl,
                        const std::vector<Launch> &fl, int32_t iters, const TParams &P, bool maxp, hipStream_t st,
                        int32_t fused_stride) {
@@ -218,12 +229,7 @@ hipError_t launch_loop(const DevGraph *gs, const DevGraph *fused, const std::vec
     if (fused)
         for (; it + 1 < iters && e == hipSuccess; it += 2)
             for (int h = 0; h < 2 && e == hipSuccess; ++h)
-                for (const Launch &L : fl) {
-                    const DevGraph *view = fused + h * fused_stride;
-                    e = L.kind == TK_PAIR ? launch_pair(view, L.items, L.n, L.a, L.b, maxp, P, L.fshape, st, true)
-                                          : launch_gen(view, L.items, L.n, maxp, P, L.a, st, true);
-                    if (e != hipSuccess) break;
-                }
+                e = launch_fused(fused + h * fused_stride, fl, P, maxp, st);
     for (; it < iters && e == hipSuccess; ++it) e = launch_iteration(gs, vl, fl, P, maxp, st);
     return e;
 }
@@ -474,12 +480,8 @@ int graph_create(lbp_ctx *ctx, const HostLayout &L, bool with_fused, char *mem, 
             fv[1].m = m2;
             fv[1].mo = g->host.m;
             DevGraph *views = (DevGraph *)ptr(gp.fdg);
-            if (L.fusable) {
-                g->fused = views;
-                g->m2 = m2;
-            } else {
-                g->tri = views;
-            }
+            (L.fusable ? g->fused : g->tri) = views;
+            g->m2 = m2;
             if (e == hipSuccess) e = hipMemcpyAsync(views, fv, sizeof(fv), hipMemcpyHostToDevice, st);
         }
         describe_lists(gp.ll, (char *)ptr(gp.items), &g->vl, &g->fl);
@@ -613,22 +615,62 @@ static bool tri_fused_wins(const std::vector<Launch> &fl, bool maxp) {
     return true;
 }
 
+static bool runs_small(const lbp_graph *g, int32_t iters, float T) {
+    return g->small.n && iters >= 2 && pair_solve_wins(g->small, T == 0.0f);
+}
+
+const DevGraph *loop_views(const lbp_graph *g, float T) {
+    if (g->use_fused) return g->fused;
+    return g->tri && tri_fused_wins(g->fl, T == 0.0f) ? g->tri : nullptr;
+}
+
 hipError_t run_graph(lbp_graph *g, int32_t iters, float d, float T) {
-    if (g->small.n && iters >= 2 && pair_solve_wins(g->small, T == 0.0f)) {
+    if (runs_small(g, iters, T)) {
         const hipError_t e =
             launch_solve_pair(g->dgraph, g->small, iters, T == 0.0f, make_params(d, T), g->ctx->stream);
         if (e == hipSuccess) return e;
         (void)hipGetLastError();  // refused (LDS size): launched iterations from here on
         g->small.n = 0;
     }
-    const DevGraph *tri = g->tri && tri_fused_wins(g->fl, T == 0.0f) ? g->tri : nullptr;
-    return run_loop(g->ctx, g->loops, g->dgraph, g->use_fused ? g->fused : tri, g->vl, g->fl, iters, d, T);
+    return run_loop(g->ctx, g->loops, g->dgraph, loop_views(g, T), g->vl, g->fl, iters, d, T);
+}
+
+// A check on a two-phase path costs a copy of the messages, two launches, the
+// residual's two and a copy back to the host; with fused views the last
+// iteration is fused too and the second buffer is the copy, and the result is
+// written where the host reads it: Potts 128 x 128 with 5 states, checked every
+// 10 iterations until settled, 374 -> 273 us a solve.
+hipError_t run_graph_residual(lbp_graph *g, int32_t iters, float d, float T, float *mprev, float *partial, float *out) {
+    hipStream_t st = g->ctx->stream;
+    const DevGraph *views = loop_views(g, T);
+    // (below two iterations a small graph is not in one workgroup anyway)
+    if (views && !runs_small(g, iters, T)) {
+        if (iters % 2 == 0) {
+            // pairs of fused iterations: the last wrote the messages from the
+            // second buffer, which still holds the iterate before
+            hipError_t e = run_loop(g->ctx, g->loops, g->dgraph, views, g->vl, g->fl, iters, d, T);
+            return e == hipSuccess ? launch_residual(g->dgraph, (int)g->E, g->m2, partial, out, st) : e;
+        }
+        hipError_t e = hipSuccess;
+        if (iters > 1) e = run_loop(g->ctx, g->loops, g->dgraph, views, g->vl, g->fl, iters - 1, d, T);
+        if (e == hipSuccess)  // one more, into the second buffer, and from there back
+            e = launch_fused(views, g->fl, make_params(d, T), T == 0.0f, st);
+        if (e == hipSuccess) e = launch_residual(g->dgraph, (int)g->E, g->m2, partial, out, st);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(g->host.m, g->m2, sizeof(float) * g->M, hipMemcpyDeviceToDevice, st);
+        return e;
+    }
+    hipError_t e = iters > 1 ? run_graph(g, iters - 1, d, T) : hipSuccess;
+    if (e == hipSuccess) e = hipMemcpyAsync(mprev, g->host.m, sizeof(float) * g->M, hipMemcpyDeviceToDevice, st);
+    if (e == hipSuccess) e = run_loop(g->ctx, g->loops, g->dgraph, nullptr, g->vl, g->fl, 1, d, T);
+    return e == hipSuccess ? launch_residual(g->dgraph, (int)g->E, mprev, partial, out, st) : e;
 }
 
 void graph_destroy(lbp_graph *g) {
     if (!g) return;
     destroy_loops(g->loops);
     if (g->conv) (void)hipFree(g->conv);
+    if (g->residual) (void)hipHostFree(g->residual);
     if (g->adj.dmem && g->adj.owns_memory) (void)hipFree(g->adj.dmem);
     if (g->owns_memory) (void)hipFree(g->dmem);
     delete g;

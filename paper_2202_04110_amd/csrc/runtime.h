@@ -74,6 +74,9 @@ hipError_t upload_lists(const LaunchLists &ll, char *mem, hipStream_t st, std::v
 
 hipError_t launch_iteration(const DevGraph *gs, const std::vector<Launch> &vl, const std::vector<Launch> &fl,
                             const TParams &P, bool maxp, hipStream_t st, int phases = 3);
+// One fused iteration of `view` (reading its m, writing its mo).
+hipError_t launch_fused(const DevGraph *view, const std::vector<Launch> &fl, const TParams &P, bool maxp,
+                        hipStream_t st);
 // `iters` iterations of fusable graphs: pairs of fused iterations through
 // the second message buffers (fused[g]: graph g's m -> m2 view,
 // fused[stride + g]: its m2 -> m view; stride = the number of graphs), then
@@ -117,7 +120,7 @@ struct lbp_graph {
     lbp::DevGraph host{};             // device pointers, host copy
     lbp::DevGraph *dgraph = nullptr;  // device copy
     lbp::DevGraph *fused = nullptr;   // device [2]: fused views over the two message buffers, or null
-    float *m2 = nullptr;              // the second message buffer of a fusable graph (device), or null
+    float *m2 = nullptr;              // the second message buffer of fused iterations (device), or null
     lbp::DevGraph *tri = nullptr;     // device [2]: the same of a graph of three-way factors, or null
     bool use_fused = false;           // lbp_run_bp runs fused iterations (chosen by the autotuner)
     bool resident_ok = false;         // small enough for the resident solver (plan below)
@@ -133,7 +136,8 @@ struct lbp_graph {
     bool has_logical = false;
     bool fusable = false;  // lane-path variables and square pairwise factors only
     uint64_t version = 0;  // bumped by every call that changes messages or inputs
-    char *conv = nullptr;  // lbp_run_bp_until workspace: previous messages, partial and final residuals
+    char *conv = nullptr;  // lbp_run_bp_until workspace: previous messages, partial residuals
+    float *residual = nullptr;  // page-locked: where its checks write their result
     // reverse-sweep workspace and the record it belongs to
     struct Adjoint {
         bool valid = false;
@@ -217,6 +221,12 @@ bool make_pair_solve(const HostLayout &L, int64_t limit_words, PairSolve *plan);
 // `iters` iterations of g on its context's stream as lbp_run_bp runs them:
 // small pairwise graphs in one workgroup, others through run_loop.
 hipError_t run_graph(lbp_graph *g, int32_t iters, float d, float T);
+// The fused views lbp_run_bp uses at temperature T, or nullptr.
+const DevGraph *loop_views(const lbp_graph *g, float T);
+// run_graph(iters >= 1), then the residual of the last iteration into out (one
+// float the device can write, page-locked host memory included); mprev: M
+// floats and partial: residual_blocks(E) floats of workspace.
+hipError_t run_graph_residual(lbp_graph *g, int32_t iters, float d, float T, float *mprev, float *partial, float *out);
 
 // Read-out (beliefs and/or MAP) on `st`; host outputs are copied with
 // hipMemcpyAsync and are complete once `st` is synchronised.
