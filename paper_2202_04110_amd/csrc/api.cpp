@@ -837,7 +837,18 @@ int lbp_sampler_create(lbp_graph *g, int32_t num_samples, lbp_sampler **out) {
         std::vector<WorkItem> mids, highs, cols;
         for (int32_t s = 0; s < S; ++s) add_to_lists(ll, s, g->shape, &mids, &highs, &cols);
         finish_lists(ll, mids, highs, cols);
+        // relay iterations: views over two message buffers a sample, and their
+        // variable launches (without, where the device has no room for them)
+        bool relay = g->relay != nullptr;
+        LaunchLists rll;
+        if (relay) {
+            std::vector<WorkItem> m, h, c;
+            const GraphShape rs = relay_shape(g->shape);
+            for (int32_t s = 0; s < S; ++s) add_to_lists(rll, s, rs, &m, &h, &c);
+            finish_lists(rll, m, h, c);
+        }
         const size_t vbytes = align256(sizeof(DevGraph) * S), lbytes = lists_bytes(ll);
+        const size_t rvbytes = align256(sizeof(DevGraph) * 2 * S), rlbytes = lists_bytes(rll);
         const size_t mb = align256(sizeof(float) * g->M), bb = align256(sizeof(float) * g->VB),
                      fb = align256(sizeof(int32_t) * 4);
         const size_t per = mb + 2 * bb + fb;
@@ -845,7 +856,15 @@ int lbp_sampler_create(lbp_graph *g, int32_t num_samples, lbp_sampler **out) {
         sp = new lbp_sampler;
         sp->g = g;
         sp->S = S;
-        hipError_t e = hipMalloc((void **)&sp->dmem, total);
+        hipError_t e = hipErrorOutOfMemory;
+        if (relay) {
+            e = hipMalloc((void **)&sp->dmem, total + rvbytes + rlbytes + mb * (size_t)S);
+            if (e != hipSuccess) {
+                (void)hipGetLastError();
+                relay = false;
+            }
+        }
+        if (!relay) e = hipMalloc((void **)&sp->dmem, total);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             delete sp;
@@ -872,6 +891,25 @@ int lbp_sampler_create(lbp_graph *g, int32_t num_samples, lbp_sampler **out) {
         sp->views = (DevGraph *)sp->dmem;
         if (e == hipSuccess) e = hipMemcpyAsync(sp->views, hv.data(), sizeof(DevGraph) * S, hipMemcpyHostToDevice, st);
         if (e == hipSuccess) e = upload_lists(ll, sp->dmem + vbytes, st, &sp->vl, &sp->fl);
+        std::vector<DevGraph> rv;
+        if (relay) {
+            char *q = sp->dmem + total;
+            sp->relay = (DevGraph *)q;
+            std::vector<Launch> fl;  // the factor launches are the same
+            if (e == hipSuccess) e = upload_lists(rll, q + rvbytes, st, &sp->relay_vl, &fl);
+            float *m2 = (float *)(q + rvbytes + rlbytes);
+            if (e == hipSuccess) e = hipMemsetAsync(m2, 0, mb * (size_t)S, st);
+            rv = hv;
+            rv.insert(rv.end(), hv.begin(), hv.end());
+            for (int32_t s = 0; s < S; ++s) {
+                float *other = m2 + mb / sizeof(float) * s;
+                rv[s].mo = other;
+                rv[S + s].m = other;
+                rv[S + s].mo = hv[s].m;
+            }
+            if (e == hipSuccess)
+                e = hipMemcpyAsync(sp->relay, rv.data(), sizeof(DevGraph) * 2 * S, hipMemcpyHostToDevice, st);
+        }
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) {
             (void)hipFree(sp->dmem);
@@ -904,7 +942,8 @@ int lbp_sampler_run(lbp_sampler *sp, int32_t iters, float damping, float tempera
         if (e == hipSuccess) e = hipMemsetAsync(sp->flag[s], 0, sizeof(int32_t) * 4, st);
     }
     if (e == hipSuccess)
-        e = run_loop(g->ctx, sp->loops, sp->views, nullptr, sp->vl, sp->fl, iters, damping, temperature);
+        e = run_loop(g->ctx, sp->loops, sp->views, sp->relay, sp->vl, sp->fl, iters, damping, temperature, sp->S,
+                     sp->relay ? &sp->relay_vl : nullptr);
     const TParams P = make_params(damping, temperature);
     const bool maxp = temperature == 0.0f;
     if (e == hipSuccess) e = launch_iteration(sp->views, sp->vl, sp->fl, P, maxp, st, 1);  // beliefs

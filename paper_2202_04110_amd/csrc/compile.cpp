@@ -409,6 +409,7 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
 
     L->edge_maddr.assign(E, 0);
     L->fac_phi.assign(F, -1);
+    std::vector<int32_t> eslot(E, -1);  // logical factors' edges: index in fvb
     int64_t M = 0, P = 0;
     auto check = [&](int64_t x, const char *what) {
         return x < INT32_MAX - 4096 ? LBP_OK : bad(err, std::string(what) + " exceeds 2^31 floats", LBP_E_UNSUPPORTED);
@@ -598,6 +599,7 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
                     const int64_t f = facs[i0 + l], e0 = d->factor_edge_off[f];
                     for (int32_t j = 0; j < k; ++j) {
                         L->edge_maddr[e0 + j] = (int32_t)(M + (int64_t)2 * j * kLanes + l);
+                        eslot[e0 + j] = ft.vb_off + j * kLanes + l;
                         L->fvb[ft.vb_off + j * kLanes + l] = vaddr[d->edge_var[e0 + j]];
                         L->fvar[ft.vb_off + j * kLanes + l] = d->edge_var[e0 + j];
                     }
@@ -624,6 +626,7 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
                 for (int32_t j = 0; j < k; ++j) {
                     const int32_t ch = j / kLanes, l = j % kLanes;
                     L->edge_maddr[e0 + j] = (int32_t)(M + (int64_t)ch * 2 * kLanes + l);
+                    eslot[e0 + j] = ft.vb_off + j;
                     L->fvb[ft.vb_off + j] = vaddr[d->edge_var[e0 + j]];
                     L->fvar[ft.vb_off + j] = d->edge_var[e0 + j];
                 }
@@ -869,6 +872,48 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
     if (L->vedge.size() >= (size_t)INT32_MAX || L->hedge.size() >= (size_t)INT32_MAX ||
         L->fvb.size() >= (size_t)INT32_MAX)
         return bad(err, "index tables exceed 2^31 entries", LBP_E_UNSUPPORTED);
+
+    // Relayed variables: two edges, both of logical factors (the products of a
+    // convolution, each the child of one AND and a parent of one OR).  A tile
+    // holding no other variable with an edge is left out of relay iterations,
+    // which pay where such tiles are most of the graph.
+    if (fill && M < (int64_t)1 << 30) {
+        auto relayed = [&](int64_t v) {
+            return degree(v) == 2 && L->vns[v] == 2 && eslot[adj[adj_off[v]]] >= 0 && eslot[adj[adj_off[v] + 1]] >= 0;
+        };
+        std::vector<char> skip(nvt, 1);
+        int64_t nskip = 0;
+        for (int64_t t = 0; t < nvt; ++t) {
+            bool any = false;
+            for (int64_t v = t * kLanes; v < std::min<int64_t>(V, (t + 1) * kLanes); ++v) {
+                if (degree(v) > 0 && L->vns[v] > 0 && !relayed(v)) skip[t] = 0;
+                any = any || relayed(v);
+            }
+            skip[t] = skip[t] && any;
+            nskip += skip[t];
+        }
+        if (2 * nskip > nvt) {
+            L->frelay.assign(L->fvb.size(), -1);
+            for (int64_t v = 0; v < V; ++v) {
+                if (!skip[v / kLanes] || !relayed(v)) continue;
+                const int64_t e0 = adj[adj_off[v]], e1 = adj[adj_off[v] + 1];
+                L->frelay[eslot[e0]] = 2 * L->edge_maddr[e1] + 1;
+                L->frelay[eslot[e1]] = 2 * L->edge_maddr[e0];
+            }
+            for (FTile &ft : L->ftile) {
+                if (ft.kind != TK_LOGL && ft.kind != TK_LOGW) continue;
+                const int32_t rows = ft.kind == TK_LOGL ? ft.a : (ft.a + kLanes - 1) / kLanes;
+                for (int32_t i = 0; i < rows * kLanes; ++i)
+                    if (L->frelay[ft.vb_off + i] >= 0) ft.relay |= 1 << (i / kLanes);
+            }
+            for (const VGroup &g : L->vgroups) {
+                VGroup r{g.bucket, {}};
+                for (int32_t t : g.tiles)
+                    if (!skip[t]) r.tiles.push_back(t);
+                L->relay_vgroups.push_back(r);
+            }
+        }
+    }
 
     // pairwise slots whose lanes hold consecutive variables (grids: nearly
     // every tile) are described by their first variable, so the fused kernel
@@ -1139,6 +1184,15 @@ int check_layout(const HostLayout &L, std::string *err) {
         if (L.fac_phi[f] >= 0 && !in(L.fac_phi[f] + (L.lp_off[f + 1] - L.lp_off[f] - 1) * kLanes, P))
             return oob("factor potential address");
     if (!in(L.zero_addr + (int64_t)kLowStatesMax * kLanes - 1, M)) return oob("zero panel");
+    if (!L.frelay.empty()) {
+        if (L.frelay.size() != L.fvb.size()) return oob("relay size");
+        for (int32_t a : L.frelay)
+            if (a < -1 || (a >= 0 && !in(a >> 1, M))) return oob("relay address");
+        if (L.relay_vgroups.size() != L.vgroups.size()) return oob("relay tiles");
+        for (const VGroup &g : L.relay_vgroups)
+            for (int32_t t : g.tiles)
+                if (!in(t, (int64_t)L.vtile.size())) return oob("relay tile");
+    }
     if (L.fvar.size() != L.fvb.size()) return oob("fvar size");
     if (L.faff.size() != 2 * L.ftile.size()) return oob("slot base size");
     for (size_t t = 0; t < L.ftile.size(); ++t)

@@ -94,6 +94,10 @@ struct HostLayout {
                                       // (kept only when compile_desc leaves the panels to fill_panels)
     std::vector<FGroup> fgroups;
     std::vector<VGroup> vgroups;
+    // Relay iterations: DevGraph::frelay and the variable tiles they still
+    // need (empty: the graph has too few relayed variables).
+    std::vector<int32_t> frelay;
+    std::vector<VGroup> relay_vgroups;
 };
 
 // Returns LBP_OK or an LBP_E_* code with a message in *err.

@@ -91,9 +91,10 @@ hipError_t launch_belief(const DevGraph *gs, const WorkItem *items, int n_low, i
 hipError_t launch_pair(const DevGraph *gs, const WorkItem *items, int n, int na, int nb, bool maxp,
                        const TParams &P, const LaunchShape &S, hipStream_t st, bool fused = false);
 // Logical tiles: wide = false for lane tiles and factors of <= 256 edges,
-// true for factors of 257..1024 edges.
+// true for factors of 257..1024 edges.  relay: relayed variables' beliefs are
+// formed here (DevGraph::frelay; G.mo must not be G.m).
 hipError_t launch_logical(const DevGraph *gs, const WorkItem *items, int n, bool wide, bool maxp, const TParams &P,
-                          const LaunchShape &S, hipStream_t st);
+                          const LaunchShape &S, hipStream_t st, bool relay = false);
 // Generic classes.  lds_code -N: dense three-way classes with N (2..4)
 // states per slot, in registers; 0: the kernel with LDS for the largest
 // class; otherwise gen_lds_code(rows bytes, summed slot states) of the

@@ -77,6 +77,7 @@ struct GGraph {
     gptr<const int32_t> vn, fac_phi, vext;
     gptr<const int64_t> lp_off;
     gptr<int32_t> flag;
+    gptr<const int32_t> frelay;
     int32_t V, E, F, zero_addr, raw_msgs;
 };
 template <class T>
@@ -109,6 +110,7 @@ __device__ __forceinline__ GGraph glob(const DevGraph &d) {
     g.vext = as_global(d.vext);
     g.lp_off = as_global(d.lp_off);
     g.flag = as_global(d.flag);
+    g.frelay = as_global(d.frelay);
     g.V = d.V;
     g.E = d.E;
     g.F = d.F;
@@ -979,30 +981,63 @@ __global__ __launch_bounds__(256) void k_pair_mix(const DevGraph *__restrict__ g
 // The leave-one-out sums are exclusive prefix + suffix sums, never total minus
 // own term.  For AND the two entries of u are swapped.
 
+// RELAY: a variable with two edges, both of logical factors, needs no belief
+// of its own: each of its factors forms it from the evidence and the other
+// edge's message (read from G.m; G.mo is another buffer, so no factor reads a
+// message another is writing), with the variable phase's additions in its
+// order.  Such variables (products of a convolution) are then in no variable
+// launch: their messages are not summed, their beliefs not written and read
+// back.  Bound by gathers of single messages across the graph.  Measured per
+// iteration without / with: deconvolution 32 x 32, 5 templates of 6 x 6, at
+// T = 0 11.5 / 11.2 us and 16 samples of it 69 / 65; 20 x 20, 3 of 4 x 4 7.8 /
+// 7.4; 13 x 13, 2 of 4 x 4 7.7 / 6.8.
+
+// belief rows (or, relayed, the evidence and the other message) of a slot
+template <class GV>
+__device__ __forceinline__ void relay_load(const GV &G, bool relay, int vb, int fr, float &b0, float &b1, float &od) {
+    if (!relay) {  // uniform
+        b0 = G.B[vb];
+        b1 = G.B[vb + kLanes];
+        return;
+    }
+    const auto src = fr >= 0 ? G.theta : G.B;
+    b0 = src[vb];
+    b1 = src[vb + kLanes];
+    od = G.m[fr >= 0 ? fr >> 1 : G.zero_addr];
+}
+// evidence + the two messages in edge order
+__device__ __forceinline__ void relay_add(int fr, float m0, float m1, float od, float &b0, float &b1) {
+    const float o0 = pk_m0(od), o1 = pk_m1(od);
+    const bool own = fr & 1;
+    const float s0 = (b0 + (own ? m0 : o0)) + (own ? o0 : m0), s1 = (b1 + (own ? m1 : o1)) + (own ? o1 : m1);
+    b0 = fr >= 0 ? s0 : b0;
+    b1 = fr >= 0 ? s1 : b1;
+}
+
 // one lane per factor, K edges (straight code for each arity: every load of
 // a step is in flight before the first is used)
-template <int K, bool MAXP, class GV>
+template <int K, bool MAXP, bool RELAY, class GV>
 __device__ __forceinline__ void logl_tile_k(const GV &G, const FTile &ft, int lane, const TParams &P) {
     constexpr int k = K, p = K - 1;
     const bool flip = ft.b != 0;
     const float *rows = G.m + ft.m_off + lane;
     float *wrows = G.mo + ft.m_off + lane;
-    float m0[K], m1[K], dl[K], dj[K], b0[K], b1[K];
-    int vb[K];
+    float m0[K], m1[K], dl[K], dj[K], b0[K], b1[K], od[K];
+    int vb[K], fr[K];
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         vb[j] = G.fvb[ft.vb_off + j * kLanes + lane];
+        fr[j] = -1;
+        if (RELAY && (ft.relay >> j & 1)) fr[j] = G.frelay[ft.vb_off + j * kLanes + lane];  // uniform test
         dj[j] = rows[(2 * j) * kLanes];  // packed binary row
     }
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-        b0[j] = G.B[vb[j]];
-        b1[j] = G.B[vb[j] + kLanes];
-    }
+    for (int j = 0; j < K; ++j) relay_load(G, RELAY && (ft.relay >> j & 1), vb[j], fr[j], b0[j], b1[j], od[j]);
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         m0[j] = pk_m0(dj[j]);
         m1[j] = pk_m1(dj[j]);
+        if (RELAY && (ft.relay >> j & 1)) relay_add(fr[j], m0[j], m1[j], od[j], b0[j], b1[j]);
         const float n0 = b0[j] - m0[j];
         const float n1 = b1[j] - m1[j];
         dl[j] = flip ? (n0 - n1) : (n1 - n0);
@@ -1068,42 +1103,41 @@ __device__ __forceinline__ void logl_tile_k(const GV &G, const FTile &ft, int la
 }
 
 // at most kLogLaneArityMax edges
-template <bool MAXP, class GV>
+template <bool MAXP, bool RELAY = false, class GV>
 __device__ __forceinline__ void logl_tile(const GV &G, const FTile &ft, int lane, const TParams &P) {
     static_assert(kLogLaneArityMax == 8, "one case per arity");
     switch (__builtin_amdgcn_readfirstlane(ft.a)) {
-    case 2: logl_tile_k<2, MAXP>(G, ft, lane, P); break;
-    case 3: logl_tile_k<3, MAXP>(G, ft, lane, P); break;
-    case 4: logl_tile_k<4, MAXP>(G, ft, lane, P); break;
-    case 5: logl_tile_k<5, MAXP>(G, ft, lane, P); break;
-    case 6: logl_tile_k<6, MAXP>(G, ft, lane, P); break;
-    case 7: logl_tile_k<7, MAXP>(G, ft, lane, P); break;
-    default: logl_tile_k<8, MAXP>(G, ft, lane, P); break;
+    case 2: logl_tile_k<2, MAXP, RELAY>(G, ft, lane, P); break;
+    case 3: logl_tile_k<3, MAXP, RELAY>(G, ft, lane, P); break;
+    case 4: logl_tile_k<4, MAXP, RELAY>(G, ft, lane, P); break;
+    case 5: logl_tile_k<5, MAXP, RELAY>(G, ft, lane, P); break;
+    case 6: logl_tile_k<6, MAXP, RELAY>(G, ft, lane, P); break;
+    case 7: logl_tile_k<7, MAXP, RELAY>(G, ft, lane, P); break;
+    default: logl_tile_k<8, MAXP, RELAY>(G, ft, lane, P); break;
     }
 }
 
 // one wavefront per factor; edge j sits in chunk j/64 at lane j%64
-template <int CH, bool MAXP, class GV>
+template <int CH, bool MAXP, bool RELAY = false, class GV>
 __device__ __forceinline__ void logw_tile(const GV &G, const FTile &ft, int lane, const TParams &P) {
     const int k = ft.a, p = k - 1;
     const int nch = (k + kLanes - 1) / kLanes;
     const bool flip = ft.b != 0;
-    float m0[CH], m1[CH], dl[CH], t[CH], pre[CH], suf[CH], dm[CH], b0[CH], b1[CH];
-    int vb[CH];
+    float m0[CH], m1[CH], dl[CH], t[CH], pre[CH], suf[CH], dm[CH], b0[CH], b1[CH], od[CH];
+    int vb[CH], fr[CH];
     // every chunk's loads before any is used (a lane past the last edge reads
     // the chunk's idle lane and the spare beliefs it points at)
 #pragma unroll
     for (int c = 0; c < CH; ++c)
         if (c < nch) {
             vb[c] = G.fvb[ft.vb_off + c * kLanes + lane];
+            fr[c] = -1;
+            if (RELAY && (ft.relay >> c & 1)) fr[c] = G.frelay[ft.vb_off + c * kLanes + lane];
             dm[c] = G.m[ft.m_off + c * 2 * kLanes + lane];  // packed binary row
         }
 #pragma unroll
     for (int c = 0; c < CH; ++c)
-        if (c < nch) {
-            b0[c] = G.B[vb[c]];
-            b1[c] = G.B[vb[c] + kLanes];
-        }
+        if (c < nch) relay_load(G, RELAY && (ft.relay >> c & 1), vb[c], fr[c], b0[c], b1[c], od[c]);
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         const int j = c * kLanes + lane;
@@ -1112,6 +1146,7 @@ __device__ __forceinline__ void logw_tile(const GV &G, const FTile &ft, int lane
         if (c < nch && j < k) {
             m0[c] = pk_m0(dm[c]);
             m1[c] = pk_m1(dm[c]);
+            if (RELAY && (ft.relay >> c & 1)) relay_add(fr[c], m0[c], m1[c], od[c], b0[c], b1[c]);
             const float n0 = b0[c] - m0[c];
             const float n1 = b1[c] - m1[c];
             dl[c] = flip ? (n0 - n1) : (n1 - n0);
@@ -1194,7 +1229,7 @@ __device__ __forceinline__ void logw_tile(const GV &G, const FTile &ft, int lane
 
 // All logical tiles of at most 4 chunks (256 edges) in one launch: a
 // wavefront runs a lane-per-factor tile or one wide factor.
-template <bool MAXP>
+template <bool MAXP, bool RELAY>
 __global__ __launch_bounds__(256) void k_logical(const DevGraph *__restrict__ gs, const WorkItem *__restrict__ items,
                                                  int nitems, TParams P, int swz) {
     const int w = wave_item(swz);
@@ -1202,12 +1237,12 @@ __global__ __launch_bounds__(256) void k_logical(const DevGraph *__restrict__ gs
     const WorkItem it = items[w];
     const GGraph G = glob(gs[it.g]);
     const FTile ft = G.ftile[it.t];
-    if (ft.kind == TK_LOGL) logl_tile<MAXP>(G, ft, lane_id(), P);
-    else logw_tile<4, MAXP>(G, ft, lane_id(), P);
+    if (ft.kind == TK_LOGL) logl_tile<MAXP, RELAY>(G, ft, lane_id(), P);
+    else logw_tile<4, MAXP, RELAY>(G, ft, lane_id(), P);
 }
 
 // logical factors of 257 .. 1024 edges
-template <bool MAXP>
+template <bool MAXP, bool RELAY>
 __global__ __launch_bounds__(256) void k_logical_wide(const DevGraph *__restrict__ gs,
                                                       const WorkItem *__restrict__ items, int nitems, TParams P,
                                                       int swz) {
@@ -1215,7 +1250,7 @@ __global__ __launch_bounds__(256) void k_logical_wide(const DevGraph *__restrict
     if (w >= nitems) return;
     const WorkItem it = items[w];
     const GGraph G = glob(gs[it.g]);
-    logw_tile<kLogWaveChunks, MAXP>(G, G.ftile[it.t], lane_id(), P);
+    logw_tile<kLogWaveChunks, MAXP, RELAY>(G, G.ftile[it.t], lane_id(), P);
 }
 
 // --------------------------------------------------------------------------
@@ -2484,17 +2519,23 @@ hipError_t launch_solve_pair(const DevGraph *g, const PairSolve &S, int32_t iter
     }
 }
 
-hipError_t launch_logical(const DevGraph *gs, const WorkItem *items, int n, bool wide, bool maxp, const TParams &P,
-                          const LaunchShape &S, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
+template <bool MAXP, bool RELAY>
+static void logical_dispatch(const DevGraph *gs, const WorkItem *items, int n, bool wide, const TParams &P,
+                             const LaunchShape &S, hipStream_t st) {
     dim3 grid(blocks_for(n, S.wpb)), block(64 * S.wpb);
-    const int z = S.swizzle;
-    if (wide) {
-        if (maxp) hipLaunchKernelGGL((k_logical_wide<true>), grid, block, 0, st, gs, items, n, P, z);
-        else hipLaunchKernelGGL((k_logical_wide<false>), grid, block, 0, st, gs, items, n, P, z);
+    if (wide) hipLaunchKernelGGL((k_logical_wide<MAXP, RELAY>), grid, block, 0, st, gs, items, n, P, S.swizzle);
+    else hipLaunchKernelGGL((k_logical<MAXP, RELAY>), grid, block, 0, st, gs, items, n, P, S.swizzle);
+}
+
+hipError_t launch_logical(const DevGraph *gs, const WorkItem *items, int n, bool wide, bool maxp, const TParams &P,
+                          const LaunchShape &S, hipStream_t st, bool relay) {
+    if (n <= 0) return hipSuccess;
+    if (relay) {
+        if (maxp) logical_dispatch<true, true>(gs, items, n, wide, P, S, st);
+        else logical_dispatch<false, true>(gs, items, n, wide, P, S, st);
     } else {
-        if (maxp) hipLaunchKernelGGL((k_logical<true>), grid, block, 0, st, gs, items, n, P, z);
-        else hipLaunchKernelGGL((k_logical<false>), grid, block, 0, st, gs, items, n, P, z);
+        if (maxp) logical_dispatch<true, false>(gs, items, n, wide, P, S, st);
+        else logical_dispatch<false, false>(gs, items, n, wide, P, S, st);
     }
     return hipGetLastError();
 }

@@ -39,7 +39,7 @@ struct FTile {
     int32_t m_off;    // message panel base
     int32_t phi_off;  // potential panel base (PAIR, GEN), 0 otherwise
     int32_t vb_off;   // base of the belief-address rows [slot or chunk][64]
-    int32_t pad;
+    int32_t relay;    // LOGL/LOGW: bit r set when row r of frelay has an entry
 };
 
 // One variable tile: 64 consecutive variables.
@@ -120,6 +120,11 @@ struct DevGraph {
     const int32_t *fac_phi;      // F: potential address of config 0, -1 logical
     const int64_t *lp_off;       // F+1
     int32_t *flag;               // non-finite read-out flag
+    // Relay iterations (null: none): for each (tile, slot, lane) of a logical
+    // factor whose variable has two edges, both of logical factors, 2 * the
+    // other edge's message address + 1 if this factor's edge is the first; -1
+    // elsewhere.
+    const int32_t *frelay;
     int32_t V, E, F, zero_addr;
     // 0: message rows of two states are packed (one value, m1 - m0, see the
     // kernels); 1: every row holds its states one per panel row (the reverse

@@ -71,6 +71,12 @@ void add_to_lists(LaunchLists &ll, int32_t gi, const GraphShape &s, std::vector<
     }
 }
 
+GraphShape relay_shape(const GraphShape &s) {
+    GraphShape r = s;
+    r.vgroups = s.relay_vgroups;
+    return r;
+}
+
 namespace {
 void merge_lists(LaunchLists &ll) {
     std::vector<size_t> sq;
@@ -190,7 +196,7 @@ hipError_t upload_lists(const LaunchLists &ll, char *mem, hipStream_t st, std::v
 }
 
 hipError_t launch_iteration(const DevGraph *gs, const std::vector<Launch> &vl, const std::vector<Launch> &fl,
-                            const TParams &P, bool maxp, hipStream_t st, int phases) {
+                            const TParams &P, bool maxp, hipStream_t st, int phases, bool relay) {
     hipError_t e = hipSuccess;
     if (phases & 1)
         for (const Launch &L : vl) {
@@ -201,8 +207,8 @@ hipError_t launch_iteration(const DevGraph *gs, const std::vector<Launch> &vl, c
         for (const Launch &L : fl) {
             switch (L.kind) {
             case TK_PAIR: e = launch_pair(gs, L.items, L.n, L.a, L.b, maxp, P, L.shape, st); break;
-            case TK_LOGL: e = launch_logical(gs, L.items, L.n, false, maxp, P, L.shape, st); break;
-            case TK_LOGW: e = launch_logical(gs, L.items, L.n, true, maxp, P, L.shape, st); break;
+            case TK_LOGL: e = launch_logical(gs, L.items, L.n, false, maxp, P, L.shape, st, relay); break;
+            case TK_LOGW: e = launch_logical(gs, L.items, L.n, true, maxp, P, L.shape, st, relay); break;
             default: e = launch_gen(gs, L.items, L.n, maxp, P, L.a, st); break;
             }
             if (e != hipSuccess) return e;
@@ -223,10 +229,14 @@ hipError_t launch_fused(const DevGraph *view, const std::vector<Launch> &fl, con
 
 hipError_t launch_loop(const DevGraph *gs, const DevGraph *fused, const std::vector<Launch> &vl,
                        const std::vector<Launch> &fl, int32_t iters, const TParams &P, bool maxp, hipStream_t st,
-                       int32_t fused_stride) {
+                       int32_t fused_stride, const std::vector<Launch> *relay) {
     hipError_t e = hipSuccess;
     int32_t it = 0;
-    if (fused)
+    if (fused && relay)
+        for (; it + 1 < iters && e == hipSuccess; it += 2)
+            for (int h = 0; h < 2 && e == hipSuccess; ++h)
+                e = launch_iteration(fused + h * fused_stride, *relay, fl, P, maxp, st, 3, true);
+    else if (fused)
         for (; it + 1 < iters && e == hipSuccess; it += 2)
             for (int h = 0; h < 2 && e == hipSuccess; ++h)
                 e = launch_fused(fused + h * fused_stride, fl, P, maxp, st);
@@ -246,12 +256,12 @@ void destroy_loops(std::vector<CachedLoop> &v) {
 
 hipError_t run_loop(lbp_ctx *ctx, std::vector<CachedLoop> &cache, const DevGraph *gs, const DevGraph *fused,
                     const std::vector<Launch> &vl, const std::vector<Launch> &fl, int32_t iters, float d, float T,
-                    int32_t fused_stride) {
+                    int32_t fused_stride, const std::vector<Launch> *relay) {
     const TParams P = make_params(d, T);
     const bool maxp = T == 0.0f;
     const size_t per_iter = vl.size() + fl.size();
     if (!ctx->use_graphs || iters < 2 || per_iter == 0)
-        return launch_loop(gs, fused, vl, fl, iters, P, maxp, ctx->stream, fused_stride);
+        return launch_loop(gs, fused, vl, fl, iters, P, maxp, ctx->stream, fused_stride, relay);
     for (const CachedLoop &c : cache)
         if (c.iters == iters && c.d == d && c.T == T) return hipGraphLaunch(c.exec, ctx->stream);
     if (!ctx->capture) {
@@ -260,7 +270,7 @@ hipError_t run_loop(lbp_ctx *ctx, std::vector<CachedLoop> &cache, const DevGraph
     }
     hipError_t e = hipStreamBeginCapture(ctx->capture, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;
-    hipError_t le = launch_loop(gs, fused, vl, fl, iters, P, maxp, ctx->capture, fused_stride);
+    hipError_t le = launch_loop(gs, fused, vl, fl, iters, P, maxp, ctx->capture, fused_stride, relay);
     hipGraph_t graph = nullptr;
     e = hipStreamEndCapture(ctx->capture, &graph);
     if (le != hipSuccess || e != hipSuccess) {
@@ -299,12 +309,14 @@ struct GraphPieces {
     size_t rev = 0, rlp = 0;
     size_t base = 0;        // device offset where the host image starts (after the raw potentials)
     size_t m, B, th, phi, ft, fvb, fvar, vt, ve, vns, hv, he, gc, gr, em, es, vs, vn, vx, fp, lp, fl, dg, q, map, items;
-    size_t m2 = 0, fdg = 0;
+    size_t m2 = 0, fdg = 0, fr = 0, ritems = 0;
     size_t data_end = 0;
     bool fused;
-    LaunchLists ll;
+    bool relay;          // with the second message buffer and views of relay iterations
+    LaunchLists ll, rll;  // the launches, and relay iterations'
 
-    GraphPieces(const HostLayout &L, bool with_fused) : fused(with_fused && (L.fusable || L.tri_fusable)) {
+    GraphPieces(const HostLayout &L, bool with_fused)
+        : fused(with_fused && (L.fusable || L.tri_fusable)), relay(with_fused && !L.frelay.empty()) {
         auto add = [&](const void *src, size_t bytes) {
             p.push_back(Piece{src, bytes, total});
             total += align256(std::max<size_t>(bytes, 4));
@@ -342,11 +354,19 @@ struct GraphPieces {
         vx = add(L.vext.data(), sizeof(int32_t) * L.vext.size());
         fp = add(L.fac_phi.data(), sizeof(int32_t) * L.fac_phi.size());
         lp = add(L.lp_off.data(), sizeof(int64_t) * L.lp_off.size());
-        GraphShape s{L.fgroups, L.vgroups, L.mids, L.highs, L.cols};
-        std::vector<WorkItem> mids, highs, cols;
-        add_to_lists(ll, 0, s, &mids, &highs, &cols);
-        finish_lists(ll, mids, highs, cols);
+        fr = add(L.frelay.data(), sizeof(int32_t) * L.frelay.size());
+        const GraphShape s{L.fgroups, L.vgroups, L.mids, L.highs, L.cols, L.relay_vgroups};
+        auto lists = [](const GraphShape &shape, LaunchLists *out) {
+            std::vector<WorkItem> mids, highs, cols;
+            add_to_lists(*out, 0, shape, &mids, &highs, &cols);
+            finish_lists(*out, mids, highs, cols);
+        };
+        lists(s, &ll);
         items = add(nullptr, lists_bytes(ll));  // packed by pack_lists
+        if (!L.frelay.empty()) {
+            lists(relay_shape(s), &rll);
+            ritems = add(nullptr, lists_bytes(rll));
+        }
         dg = add(nullptr, sizeof(DevGraph));    // written into the image by graph_create
         data_end = total;  // everything above is copied from the host image, everything below starts zero
         m = add(nullptr, sizeof(float) * L.M);
@@ -358,7 +378,7 @@ struct GraphPieces {
         }
         q = add(nullptr, sizeof(float) * L.VS);
         map = add(nullptr, sizeof(int32_t) * L.V);
-        if (fused) {
+        if (fused || relay) {
             m2 = add(nullptr, sizeof(float) * L.M);
             fdg = add(nullptr, sizeof(DevGraph) * 2);
         }
@@ -382,6 +402,7 @@ int graph_fill_image(const HostLayout &L, char *image, const lbp_graph_desc *d) 
     for (const Piece &p : gp.p)
         if (p.src && p.bytes) std::memcpy(at(p.off), p.src, p.bytes);
     pack_lists(gp.ll, at(gp.p[gp.items].off));
+    if (!L.frelay.empty()) pack_lists(gp.rll, at(gp.p[gp.ritems].off));
     if (!gp.raw) return LBP_OK;
     // the evidence as given (graph_create scatters it into its panel)
     if (!d) return set_error(LBP_E_INVALID, "graph image: the layout has no panels and no description was given");
@@ -449,6 +470,7 @@ int graph_create(lbp_ctx *ctx, const HostLayout &L, bool with_fused, char *mem, 
         h.fac_phi = (const int32_t *)ptr(gp.fp);
         h.lp_off = (const int64_t *)ptr(gp.lp);
         h.flag = (int32_t *)ptr(gp.fl);
+        h.frelay = L.frelay.empty() ? nullptr : (const int32_t *)ptr(gp.fr);
         h.V = (int32_t)L.V;
         h.E = (int32_t)L.E;
         h.F = (int32_t)L.F;
@@ -472,7 +494,7 @@ int graph_create(lbp_ctx *ctx, const HostLayout &L, bool with_fused, char *mem, 
             if (e == hipSuccess) e = launch_logpot_in(g->dgraph, (int)L.F, (const float *)ptr(gp.rlp), st);
         }
         DevGraph fv[2];
-        if (gp.fused) {
+        if (gp.fused || gp.relay) {
             float *m2 = (float *)ptr(gp.m2);
             fv[0] = g->host;
             fv[0].mo = m2;
@@ -480,14 +502,18 @@ int graph_create(lbp_ctx *ctx, const HostLayout &L, bool with_fused, char *mem, 
             fv[1].m = m2;
             fv[1].mo = g->host.m;
             DevGraph *views = (DevGraph *)ptr(gp.fdg);
-            (L.fusable ? g->fused : g->tri) = views;
+            (gp.relay ? g->relay : L.fusable ? g->fused : g->tri) = views;
             g->m2 = m2;
             if (e == hipSuccess) e = hipMemcpyAsync(views, fv, sizeof(fv), hipMemcpyHostToDevice, st);
         }
         describe_lists(gp.ll, (char *)ptr(gp.items), &g->vl, &g->fl);
+        if (gp.relay) {
+            std::vector<Launch> fl;  // the factor launches are the same
+            describe_lists(gp.rll, (char *)ptr(gp.ritems), &g->relay_vl, &fl);
+        }
         // the host image and the descriptors must outlive the copies (the
         // descriptors live in g; without wait, the caller keeps the image)
-        if (e == hipSuccess && (wait || gp.fused)) e = hipStreamSynchronize(st);
+        if (e == hipSuccess && (wait || gp.fused || gp.relay)) e = hipStreamSynchronize(st);
         if (e != hipSuccess) (void)hipStreamSynchronize(st);  // no copy may still read an image
         panel_free(own_image);
         own_image = nullptr;
@@ -496,7 +522,7 @@ int graph_create(lbp_ctx *ctx, const HostLayout &L, bool with_fused, char *mem, 
             delete g;
             return hip_error(e, "graph upload");
         }
-        g->shape = GraphShape{L.fgroups, L.vgroups, L.mids, L.highs, L.cols};
+        g->shape = GraphShape{L.fgroups, L.vgroups, L.mids, L.highs, L.cols, L.relay_vgroups};
         for (const FGroup &fg : L.fgroups)
             if (fg.kind == TK_LOGL || fg.kind == TK_LOGW) g->has_logical = true;
         g->fusable = L.fusable;
@@ -621,7 +647,12 @@ static bool runs_small(const lbp_graph *g, int32_t iters, float T) {
 
 const DevGraph *loop_views(const lbp_graph *g, float T) {
     if (g->use_fused) return g->fused;
+    if (g->relay) return g->relay;
     return g->tri && tri_fused_wins(g->fl, T == 0.0f) ? g->tri : nullptr;
+}
+
+static const std::vector<Launch> *loop_relay(const lbp_graph *g) {
+    return g->relay && !g->use_fused ? &g->relay_vl : nullptr;
 }
 
 hipError_t run_graph(lbp_graph *g, int32_t iters, float d, float T) {
@@ -632,7 +663,7 @@ hipError_t run_graph(lbp_graph *g, int32_t iters, float d, float T) {
         (void)hipGetLastError();  // refused (LDS size): launched iterations from here on
         g->small.n = 0;
     }
-    return run_loop(g->ctx, g->loops, g->dgraph, loop_views(g, T), g->vl, g->fl, iters, d, T);
+    return run_loop(g->ctx, g->loops, g->dgraph, loop_views(g, T), g->vl, g->fl, iters, d, T, 1, loop_relay(g));
 }
 
 // A check on a two-phase path costs a copy of the messages, two launches, the
@@ -643,18 +674,21 @@ hipError_t run_graph(lbp_graph *g, int32_t iters, float d, float T) {
 hipError_t run_graph_residual(lbp_graph *g, int32_t iters, float d, float T, float *mprev, float *partial, float *out) {
     hipStream_t st = g->ctx->stream;
     const DevGraph *views = loop_views(g, T);
+    const std::vector<Launch> *relay = loop_relay(g);
     // (below two iterations a small graph is not in one workgroup anyway)
     if (views && !runs_small(g, iters, T)) {
         if (iters % 2 == 0) {
             // pairs of fused iterations: the last wrote the messages from the
             // second buffer, which still holds the iterate before
-            hipError_t e = run_loop(g->ctx, g->loops, g->dgraph, views, g->vl, g->fl, iters, d, T);
+            hipError_t e = run_loop(g->ctx, g->loops, g->dgraph, views, g->vl, g->fl, iters, d, T, 1, relay);
             return e == hipSuccess ? launch_residual(g->dgraph, (int)g->E, g->m2, partial, out, st) : e;
         }
         hipError_t e = hipSuccess;
-        if (iters > 1) e = run_loop(g->ctx, g->loops, g->dgraph, views, g->vl, g->fl, iters - 1, d, T);
+        if (iters > 1) e = run_loop(g->ctx, g->loops, g->dgraph, views, g->vl, g->fl, iters - 1, d, T, 1, relay);
+        const TParams P = make_params(d, T);
         if (e == hipSuccess)  // one more, into the second buffer, and from there back
-            e = launch_fused(views, g->fl, make_params(d, T), T == 0.0f, st);
+            e = relay ? launch_iteration(views, *relay, g->fl, P, T == 0.0f, st, 3, true)
+                      : launch_fused(views, g->fl, P, T == 0.0f, st);
         if (e == hipSuccess) e = launch_residual(g->dgraph, (int)g->E, g->m2, partial, out, st);
         if (e == hipSuccess)
             e = hipMemcpyAsync(g->host.m, g->m2, sizeof(float) * g->M, hipMemcpyDeviceToDevice, st);

@@ -72,8 +72,11 @@ void pack_lists(const LaunchLists &ll, char *host);
 hipError_t upload_lists(const LaunchLists &ll, char *mem, hipStream_t st, std::vector<Launch> *vl,
                         std::vector<Launch> *fl);
 
+// relay: gs has separate message buffers (m read, mo written) and vl is the
+// relay iterations' variable launches: logical factors form their relayed
+// variables' beliefs themselves.
 hipError_t launch_iteration(const DevGraph *gs, const std::vector<Launch> &vl, const std::vector<Launch> &fl,
-                            const TParams &P, bool maxp, hipStream_t st, int phases = 3);
+                            const TParams &P, bool maxp, hipStream_t st, int phases = 3, bool relay = false);
 // One fused iteration of `view` (reading its m, writing its mo).
 hipError_t launch_fused(const DevGraph *view, const std::vector<Launch> &fl, const TParams &P, bool maxp,
                         hipStream_t st);
@@ -82,9 +85,11 @@ hipError_t launch_fused(const DevGraph *view, const std::vector<Launch> &fl, con
 // fused[stride + g]: its m2 -> m view; stride = the number of graphs), then
 // one two-phase in-place iteration on gs if iters is odd, so the messages end
 // in each graph's own buffer.  Bitwise the same as two-phase iterations.
+// relay: `fused` are views of relay iterations, whose variable launches these
+// are (pairs of relay iterations in place of fused ones).
 hipError_t launch_loop(const DevGraph *gs, const DevGraph *fused, const std::vector<Launch> &vl,
                        const std::vector<Launch> &fl, int32_t iters, const TParams &P, bool maxp, hipStream_t st,
-                       int32_t fused_stride = 1);
+                       int32_t fused_stride = 1, const std::vector<Launch> *relay = nullptr);
 
 // A captured fixed-iteration loop, replayed with hipGraphLaunch.
 struct CachedLoop {
@@ -99,7 +104,10 @@ struct GraphShape {
     std::vector<FGroup> fgroups;
     std::vector<VGroup> vgroups;
     std::vector<int32_t> mids, highs, cols;
+    std::vector<VGroup> relay_vgroups;  // empty: no relay iterations
 };
+// The shape whose variable launches are those of relay iterations.
+GraphShape relay_shape(const GraphShape &s);
 
 }  // namespace lbp
 
@@ -121,6 +129,8 @@ struct lbp_graph {
     lbp::DevGraph *dgraph = nullptr;  // device copy
     lbp::DevGraph *fused = nullptr;   // device [2]: fused views over the two message buffers, or null
     float *m2 = nullptr;              // the second message buffer of fused iterations (device), or null
+    lbp::DevGraph *relay = nullptr;   // device [2]: views of relay iterations, or null
+    std::vector<lbp::Launch> relay_vl;  // their variable launches
     lbp::DevGraph *tri = nullptr;     // device [2]: the same of a graph of three-way factors, or null
     bool use_fused = false;           // lbp_run_bp runs fused iterations (chosen by the autotuner)
     bool resident_ok = false;         // small enough for the resident solver (plan below)
@@ -169,6 +179,8 @@ struct lbp_sampler {
     int32_t S = 0;
     char *dmem = nullptr;
     lbp::DevGraph *views = nullptr;  // device [S]: the graph with sample s's messages, beliefs, evidence
+    lbp::DevGraph *relay = nullptr;  // device [2 * S]: the samples' views of relay iterations, or null
+    std::vector<lbp::Launch> relay_vl;
     std::vector<float *> m;          // sample s's message panels (device)
     std::vector<int32_t *> flag;     // sample s's read-out flags (device)
     std::vector<lbp::Launch> vl, fl;
@@ -183,7 +195,7 @@ namespace lbp {
 // fused: the graph's fused views (nullptr for two-phase iterations).
 hipError_t run_loop(lbp_ctx *ctx, std::vector<CachedLoop> &cache, const DevGraph *gs, const DevGraph *fused,
                     const std::vector<Launch> &vl, const std::vector<Launch> &fl, int32_t iters, float d, float T,
-                    int32_t fused_stride = 1);
+                    int32_t fused_stride = 1, const std::vector<Launch> *relay = nullptr);
 
 // Device bytes an uploaded layout occupies (with_fused: plus the second
 // message buffer and views of the fused iteration, if the layout allows it).
