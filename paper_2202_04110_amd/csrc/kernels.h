@@ -86,10 +86,22 @@ struct AdjBufs {
 // (indices into the graph's hvar list); bucket >= states of every low lane.
 hipError_t launch_belief(const DevGraph *gs, const WorkItem *items, int n_low, int n_mid, int n_high, int bucket,
                          const LaunchShape &S, hipStream_t st);
+// Fused launches that may run two wavefronts a tile (half: the graph's
+// variables have at most four edges) do up to this many tiles, the second
+// figure for max-product.  Measured at T = 1, one wavefront / two, us per
+// iteration (tiles in brackets): five states 50 x 50 (80) 3.60 / 3.24, 100 x 100
+// (320) 3.81 / 3.63; four, 125 x 125 (490) 3.48 / 3.61; eight, 90 x 90 (256)
+// 4.90 / 4.69, 126 x 126 (510) 5.28 / 5.45; two, 125 x 125 2.89 / 2.62.  At
+// T = 0: two states 2.81 / 2.61, three 64 x 64 2.79 / 2.72, five 100 x 100
+// 3.31 / 3.43.  Random pairs of up to twelve edges a variable 5.97 / 7.28.
+constexpr bool pair_half_wins(int n, int tiles, bool maxp) {
+    return n == 2 ? tiles <= 512 : maxp ? n == 3 && tiles <= 160 : tiles <= 384;
+}
 // fused: one whole iteration in the factor launch (square classes only; see
 // pair_tile), reading G.m and writing G.mo.
 hipError_t launch_pair(const DevGraph *gs, const WorkItem *items, int n, int na, int nb, bool maxp,
-                       const TParams &P, const LaunchShape &S, hipStream_t st, bool fused = false);
+                       const TParams &P, const LaunchShape &S, hipStream_t st, bool fused = false,
+                       bool half = false);
 // Logical tiles: wide = false for lane tiles and factors of <= 256 edges,
 // true for factors of 257..1024 edges.  relay: relayed variables' beliefs are
 // formed here (DevGraph::frelay; G.mo must not be G.m).

@@ -484,6 +484,30 @@ __device__ __forceinline__ void belief_regs2(const GV &G, PT mm, int va, int vb,
     belief_regs2<NA, NB, MODE, false>(G, mm, va, vb, ba, bb, fa, fb, mm, ba, bb);
 }
 
+// One lane-path variable's belief, as belief_regs2.
+template <int N, int MODE, class GV>
+__device__ __forceinline__ void belief_regs1(const GV &G, int v, float (&b)[N]) {
+    constexpr int KU = 4;
+    const int l = v & (kLanes - 1);
+    const VTile t = G.vtile[v >> 6];
+#pragma unroll
+    for (int s = 0; s < N; ++s) b[s] = G.theta[t.b_off + l + s * kLanes];
+    const int32_t *ea = G.vedge + t.e_off + l;
+    for (int k0 = 0; k0 < t.kmax; k0 += KU) {
+        int a[KU];
+#pragma unroll
+        for (int u = 0; u < KU; ++u) a[u] = ea[min(k0 + u, t.kmax - 1) * kLanes];
+        float x[KU][N];
+#pragma unroll
+        for (int u = 0; u < KU; ++u)
+            msg_load<N, MODE>(G.m + (k0 + u < t.kmax ? a[u] : G.zero_addr), N, 0, true, x[u]);
+#pragma unroll
+        for (int u = 0; u < KU; ++u)
+#pragma unroll
+            for (int s = 0; s < N; ++s) b[s] += x[u][s];
+    }
+}
+
 // The beliefs of three lane-path variables of N states, as belief_regs2.
 template <int N, int MODE, class GV>
 __device__ __forceinline__ void belief_regs3(const GV &G, const int (&v)[3], float (&b)[3][N]) {
@@ -940,6 +964,73 @@ __global__ __launch_bounds__(256) void k_pair(const DevGraph *__restrict__ gs, c
     const GGraph G = glob(gs[it.g]);
     const FTile ft = G.ftile[it.t];
     pair_tile<NA, NB, EXACT, MAXP, FUSED, EARLY>(G, ft, lane_id(), P, it.t);
+}
+
+// One fused iteration of a small graph, two wavefronts a tile: one makes the
+// factors' messages to slot 0, the other to slot 1.  Each needs the belief of
+// one slot only, so its gather and its serial chain of additions and
+// exponentials are half of pair_tile's, in the same order (bitwise the same);
+// the tables are read twice.  Below a wavefront per SIMD an iteration's time is
+// one wavefront's chain, so halving it pays until the second reading and the
+// doubled wavefronts cost as much (pair_half_wins, with both measured): Potts
+// 64 x 64 with six states at T = 1 3.93 -> 3.57 us per iteration.
+template <int N, bool MAXP, int SLOT, class GV>
+__device__ __forceinline__ void pair_half_tile(const GV &G, const FTile &ft, int lane, const TParams &P, int t) {
+    constexpr int MODE = N == 2 ? 2 : 0;
+    const float *r0 = G.m + ft.m_off + lane, *r1 = r0 + N * kLanes;
+    const float *ph = G.phi + ft.phi_off + lane;
+    // the other slot's variable (an idle lane works on lane 0's; its result is not used)
+    const int base = G.faff[2 * t + 1 - SLOT];
+    int v = base >= 0 ? (lane < ft.nact ? base + lane : -1) : G.fvar[ft.vb_off + (1 - SLOT) * kLanes + lane];
+    const int v0 = __builtin_amdgcn_readfirstlane(v);
+    v = v < 0 ? v0 : v;
+    // table entries by (state of SLOT, state of the other)
+    float p[N][N];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j) p[i][j] = ph[(SLOT == 0 ? i * N + j : j * N + i) * kLanes];
+    float own[N], other[N], x[N];
+    msg_load<N, MODE>(SLOT == 0 ? r0 : r1, N, 0, true, own);
+    msg_load<N, MODE>(SLOT == 0 ? r1 : r0, N, 0, true, other);
+    belief_regs1<N, MODE>(G, v, x);
+#pragma unroll
+    for (int j = 0; j < N; ++j) x[j] = x[j] - other[j];
+    float u[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        float e[N];
+        float M = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            e[j] = p[i][j] + x[j];
+            M = fmaxf(M, e[j]);
+        }
+        if (MAXP) {
+            u[i] = M;
+        } else if (N == 2) {
+            u[i] = lse2(e[0], e[1], M, P);
+        } else {
+            float sum = 0.0f;
+#pragma unroll
+            for (int j = 0; j < N; ++j) sum += fexp2((e[j] - M) * P.c);
+            u[i] = M + flog2(sum) * P.r;
+        }
+    }
+    float *w = G.mo + ft.m_off + lane + SLOT * N * kLanes;
+    damp_store<N>(w, own, u, N, P);
+}
+
+template <int N, bool MAXP>
+__global__ __launch_bounds__(256) void k_pair_half(const DevGraph *__restrict__ gs, const WorkItem *__restrict__ items,
+                                                   int nitems, TParams P) {
+    const int w = wave_index(4);
+    if (w >= 2 * nitems) return;
+    const WorkItem it = items[w >> 1];
+    const GGraph G = glob(gs[it.g]);
+    const FTile ft = G.ftile[it.t];
+    if (w & 1) pair_half_tile<N, MAXP, 1>(G, ft, lane_id(), P, it.t);
+    else pair_half_tile<N, MAXP, 0>(G, ft, lane_id(), P, it.t);
 }
 
 // Square pairwise tiles of several state counts (2..8) in one launch: each
@@ -2423,11 +2514,30 @@ static void pair_dispatch(const DevGraph *gs, const WorkItem *items, int n, int 
 }
 
 hipError_t launch_pair(const DevGraph *gs, const WorkItem *items, int n, int na, int nb, bool maxp,
-                       const TParams &P, const LaunchShape &S, hipStream_t st, bool fused) {
+                       const TParams &P, const LaunchShape &S, hipStream_t st, bool fused, bool half) {
     if (n <= 0) return hipSuccess;
     // na = nb = 0: a mixed launch of square tiles of 2..kPairStatesMax states
     if (na != nb && (na == 0 || nb == 0)) return hipErrorInvalidValue;
     if (fused && na != 0 && (na != nb || na < 2 || na > kPairStatesMax)) return hipErrorInvalidValue;
+    if (fused && half && na != 0 && pair_half_wins(na, n, maxp)) {
+        const dim3 grid(blocks_for(2 * n, 4)), block(256);
+#define HALF_CASE(N)                                                                                \
+    case N:                                                                                         \
+        if (maxp) hipLaunchKernelGGL((k_pair_half<N, true>), grid, block, 0, st, gs, items, n, P);  \
+        else hipLaunchKernelGGL((k_pair_half<N, false>), grid, block, 0, st, gs, items, n, P);      \
+        return hipGetLastError();
+        switch (na) {
+            HALF_CASE(2)
+            HALF_CASE(3)
+            HALF_CASE(4)
+            HALF_CASE(5)
+            HALF_CASE(6)
+            HALF_CASE(7)
+            HALF_CASE(8)
+        default: return hipErrorInvalidValue;
+        }
+#undef HALF_CASE
+    }
     if (fused && S.early) {
         if (maxp) pair_dispatch<true, true, true>(gs, items, n, na, nb, P, S, st);
         else pair_dispatch<false, true, true>(gs, items, n, na, nb, P, S, st);

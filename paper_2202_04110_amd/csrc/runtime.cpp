@@ -220,7 +220,7 @@ hipError_t launch_fused(const DevGraph *view, const std::vector<Launch> &fl, con
                         hipStream_t st) {
     hipError_t e = hipSuccess;
     for (const Launch &L : fl) {
-        e = L.kind == TK_PAIR ? launch_pair(view, L.items, L.n, L.a, L.b, maxp, P, L.fshape, st, true)
+        e = L.kind == TK_PAIR ? launch_pair(view, L.items, L.n, L.a, L.b, maxp, P, L.fshape, st, true, L.half)
                               : launch_gen(view, L.items, L.n, maxp, P, L.a, st, true);
         if (e != hipSuccess) break;
     }
@@ -507,6 +507,9 @@ int graph_create(lbp_ctx *ctx, const HostLayout &L, bool with_fused, char *mem, 
             if (e == hipSuccess) e = hipMemcpyAsync(views, fv, sizeof(fv), hipMemcpyHostToDevice, st);
         }
         describe_lists(gp.ll, (char *)ptr(gp.items), &g->vl, &g->fl);
+        bool four = L.fusable;
+        for (const VTile &vt : L.vtile) four = four && vt.kmax <= 4;
+        for (Launch &x : g->fl) x.half = four;
         if (gp.relay) {
             std::vector<Launch> fl;  // the factor launches are the same
             describe_lists(gp.rll, (char *)ptr(gp.ritems), &g->relay_vl, &fl);
@@ -876,7 +879,7 @@ int adjoint_backward(lbp_graph *g, const float *grad_q, float *grad_logpot, floa
             for (int32_t j = 0; j + 1 < len && e == hipSuccess; ++j)
                 for (const Launch &L : g->fl)
                     if (e == hipSuccess)
-                        e = launch_pair(J.views + j, L.items, L.n, L.a, L.b, false, P, L.fshape, st, true);
+                        e = launch_pair(J.views + j, L.items, L.n, L.a, L.b, false, P, L.fshape, st, true, L.half);
             for (int32_t j = len - 1; j >= 0 && e == hipSuccess; --j) {
                 B.nbar = nbar[cur ^ 1];
                 for (const Launch &L : g->fl)
