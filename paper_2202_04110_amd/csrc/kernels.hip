@@ -552,9 +552,17 @@ __device__ __forceinline__ void belief_regs3(const GV &G, const int (&v)[3], flo
 // wavefront of one variable is a few dozen instructions behind four dependent
 // loads, and a deconvolution graph has thousands: grouped, the launch has a
 // quarter of the wavefronts: 16 deconvolution samples of 200 iterations
-// 15.7 -> 13.8 ms (with the logical lane tiles' straight code below), one
-// deconvolution solve unchanged (bound by the launches' latency).
+// 15.7 -> 13.8 ms (with the logical lane tiles' straight code below).
+// As many as the chip holds at once (32 wavefronts on each of 256 CUs) take one
+// a wavefront: none of them waits for another to end, and a group's chain is
+// the longer one.  One against four, sweeps in us: RBM 60x500 (500 of them)
+// 503 / 609, 122x31 598 / 643, a 32x32 deconvolution (4205) 2099 / 2246; two
+// 32x32 samples (9000) 1339 / 1344, four 2085 / 1957, sixteen 5918 / 5329.
 constexpr int kMidGroup = 4;
+constexpr int kMidAlone = 8192;
+__host__ __device__ inline int mid_waves(int n_mid) {
+    return n_mid <= kMidAlone ? n_mid : (n_mid + kMidGroup - 1) / kMidGroup;
+}
 template <class GV>
 __device__ __forceinline__ void belief_mid_var(const GV &G, int hv, int lane);
 __device__ __forceinline__ void belief_mid_group(const DevGraph *__restrict__ gs, const WorkItem *__restrict__ items,
@@ -802,7 +810,7 @@ __global__ __launch_bounds__(256, HIGH && NB <= 8 ? 8 : 1) void k_belief(const D
         }
         return;
     }
-    const int nwave = n_low + (n_mid + kMidGroup - 1) / kMidGroup;
+    const int nwave = n_low + mid_waves(n_mid);
     const int wave_blocks = (nwave + 3) / 4;
     const int bx = (int)blockIdx.x - n_high;
     const int b = swz ? swizzle_block(bx, wave_blocks) : bx;
@@ -811,6 +819,9 @@ __global__ __launch_bounds__(256, HIGH && NB <= 8 ? 8 : 1) void k_belief(const D
     if (w < n_low) {
         const WorkItem it = items[w];
         belief_low_tile<NB>(glob(gs[it.g]), it.t, lane_id());
+    } else if (n_mid <= kMidAlone) {
+        const WorkItem it = items[w];
+        belief_mid_var(glob(gs[it.g]), it.t, lane_id());
     } else {
         belief_mid_group(gs, items + n_low, (w - n_low) * kMidGroup, n_mid, lane_id());
     }
@@ -2467,7 +2478,7 @@ inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1)
 hipError_t launch_belief(const DevGraph *gs, const WorkItem *items, int n_low, int n_mid, int n_high, int bucket,
                          const LaunchShape &S, hipStream_t st) {
     if (n_low + n_mid + n_high <= 0) return hipSuccess;
-    dim3 grid(blocks_for(n_low + (n_mid + kMidGroup - 1) / kMidGroup, 4) + n_high), block(256);
+    dim3 grid(blocks_for(n_low + mid_waves(n_mid), 4) + n_high), block(256);
     const int z = S.swizzle;
 #define BELIEF_CASE(NB)                                                                                       \
     if (n_high > 0) hipLaunchKernelGGL((k_belief<NB, true>), grid, block, 0, st, gs, items, n_low, n_mid, n_high, z); \

@@ -76,3 +76,22 @@ def test_beliefs_match_the_sums(lbp, ctx, name):
     tol = np.repeat(deg, spec.var_num_states) * 2.0 ** -24 * mag
     assert (np.abs(b - want) <= tol).all(), float((np.abs(b - want) - tol).max())
     g.free()
+
+
+@pytest.mark.parametrize("nv", [8192, 8193, 8198])
+def test_one_or_four_variables_a_wavefront(lbp, ctx, nv):
+    """A wavefront each up to 8192 variables of 17 to 64 edges, four to a
+    wavefront (the last one short) above."""
+    spec = W.rbm(nv, 17, seed=5)
+    g = lbp.Graph(ctx, spec)
+    m = np.random.default_rng(4).normal(0, 2, (spec.num_edges, 2)).astype(np.float32)
+    m -= m.max(1, keepdims=True)
+    g.set_messages(m.reshape(-1))
+    b = g.get_beliefs(normalized=False).astype(np.float64).reshape(-1, 2)
+    want = spec.evidence.astype(np.float64).reshape(-1, 2).copy()
+    mag = np.abs(want)
+    np.add.at(want, spec.edge_var, m.astype(np.float64))
+    np.add.at(mag, spec.edge_var, np.abs(m.astype(np.float64)))
+    tol = np.bincount(spec.edge_var, minlength=spec.num_vars)[:, None] * 2.0 ** -24 * mag
+    assert (np.abs(b - want) <= tol).all(), float((np.abs(b - want) - tol).max())
+    g.free()
