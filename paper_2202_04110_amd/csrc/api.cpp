@@ -770,12 +770,13 @@ int lbp_batch_create(lbp_ctx *ctx, lbp_graph *const *graphs, int32_t num_graphs,
             delete b;
             return fail(LBP_E_OOM, "batch allocation failed");
         }
-        // descriptors, then (when every graph has a fused form) each graph's
-        // m -> m2 view and then each graph's m2 -> m view
+        // descriptors, then (when every graph has pairwise fused iterations;
+        // other graphs' second buffers serve forms of a lone graph) each
+        // graph's m -> m2 view and then each graph's m2 -> m view
         std::vector<DevGraph> hg;
         for (int32_t gi = 0; gi < num_graphs; ++gi) hg.push_back(graphs[gi]->host);
         bool fusable = num_graphs > 0;
-        for (int32_t gi = 0; gi < num_graphs; ++gi) fusable = fusable && graphs[gi]->m2;
+        for (int32_t gi = 0; gi < num_graphs; ++gi) fusable = fusable && graphs[gi]->fused;
         if (fusable) {
             for (int32_t gi = 0; gi < num_graphs; ++gi) {
                 hg.push_back(graphs[gi]->host);

@@ -219,6 +219,9 @@ hipError_t launch_iteration(const DevGraph *gs, const std::vector<Launch> &vl, c
 hipError_t launch_fused(const DevGraph *view, const std::vector<Launch> &fl, const TParams &P, bool maxp,
                         hipStream_t st) {
     hipError_t e = hipSuccess;
+    // no launch before every one is known to have a fused form
+    for (const Launch &L : fl)
+        if (L.kind != TK_PAIR && (L.kind != TK_GEN || L.a >= 0)) return hipErrorInvalidValue;
     for (const Launch &L : fl) {
         e = L.kind == TK_PAIR ? launch_pair(view, L.items, L.n, L.a, L.b, maxp, P, L.fshape, st, true, L.half)
                               : launch_gen(view, L.items, L.n, maxp, P, L.a, st, true);
