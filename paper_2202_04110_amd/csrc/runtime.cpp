@@ -428,6 +428,12 @@ int graph_create(lbp_ctx *ctx, const HostLayout &L, bool with_fused, char *mem, 
             g->owns_memory = false;
         } else {
             hipError_t e = hipMalloc((void **)&g->dmem, gp.total);
+            if (e != hipSuccess && (gp.relay || (gp.fused && !L.fusable))) {
+                // no room for the second message buffer, which these forms can do without
+                (void)hipGetLastError();
+                gp = GraphPieces(L, false);
+                e = hipMalloc((void **)&g->dmem, gp.total);
+            }
             if (e != hipSuccess) {
                 delete g;
                 (void)hipGetLastError();
