@@ -453,13 +453,18 @@ std::vector<Launch *> all_launches(std::vector<Launch> &vl, std::vector<Launch> 
 }
 
 // Times `reps` whole two-phase iterations with the groups' current shapes
-// (after one warm-up iteration).
-hipError_t time_iterations(const DevGraph *gs, const std::vector<Launch> &vl, const std::vector<Launch> &fl,
-                           const TParams &P, bool maxp, hipStream_t st, int reps, hipEvent_t a, hipEvent_t b,
-                           float *ms) {
-    hipError_t e = launch_iteration(gs, vl, fl, P, maxp, st, 3);
+// (after one warm-up iteration); with relay views, relay iterations of vl
+// (their variable launches) through the two views in turn.
+hipError_t time_iterations(const DevGraph *gs, const DevGraph *relay, const std::vector<Launch> &vl,
+                           const std::vector<Launch> &fl, const TParams &P, bool maxp, hipStream_t st, int reps,
+                           hipEvent_t a, hipEvent_t b, float *ms) {
+    auto one = [&](int r) {
+        return relay ? launch_iteration(relay + (r & 1), vl, fl, P, maxp, st, 3, true)
+                     : launch_iteration(gs, vl, fl, P, maxp, st, 3);
+    };
+    hipError_t e = one(1);
     if (e == hipSuccess) e = hipEventRecord(a, st);
-    for (int r = 0; r < reps && e == hipSuccess; ++r) e = launch_iteration(gs, vl, fl, P, maxp, st, 3);
+    for (int r = 0; r < reps && e == hipSuccess; ++r) e = one(r);
     if (e == hipSuccess) e = hipEventRecord(b, st);
     if (e == hipSuccess) e = hipEventSynchronize(b);
     if (e == hipSuccess) e = hipEventElapsedTime(ms, a, b);
@@ -475,9 +480,10 @@ hipError_t time_iterations(const DevGraph *gs, const std::vector<Launch> &vl, co
 // launch at a time sees what one phase leaves in the XCDs' L2 for the next:
 // a bipartite layer's factor tiles swizzled into per-XCD runs are read by
 // the column groups of the same XCD (RBM 784x500: 9.1 against 10.6 us per
-// iteration unswizzled), which a launch timed alone cannot show.
-int tune_launches(const DevGraph *gs, std::vector<Launch> &vl, std::vector<Launch> &fl, float d, float T, int reps,
-                  hipStream_t st, float *best_ms) {
+// iteration unswizzled), which a launch timed alone cannot show.  relay as for
+// time_iterations.
+int tune_launches(const DevGraph *gs, const DevGraph *relay, std::vector<Launch> &vl, std::vector<Launch> &fl,
+                  float d, float T, int reps, hipStream_t st, float *best_ms) {
     const TParams P = make_params(d, T);
     const bool maxp = T == 0.0f;
     hipEvent_t a, b;
@@ -505,7 +511,7 @@ int tune_launches(const DevGraph *gs, std::vector<Launch> &vl, std::vector<Launc
             for (const LaunchShape &c : cand) {
                 L->shape = c;
                 float ms = 0.0f;
-                e = time_iterations(gs, vl, fl, P, maxp, st, reps, a, b, &ms);
+                e = time_iterations(gs, relay, vl, fl, P, maxp, st, reps, a, b, &ms);
                 if (e != hipSuccess) break;
                 if (ms < best_t) {
                     best_t = ms;
@@ -620,6 +626,7 @@ int lbp_graph_set_launch(lbp_graph *g, int32_t i, int32_t waves_per_block, int32
     (void)hipStreamSynchronize(g->ctx->stream);
     destroy_loops(g->loops);
     L.shape = LaunchShape{waves_per_block, swizzle};
+    if (i < nv && g->relay) g->relay_vl[i].shape = L.shape;
     return LBP_OK;
 }
 
@@ -655,8 +662,13 @@ int lbp_autotune(lbp_graph *g, float damping, float temperature, int32_t reps, f
         return fail(LBP_E_OOM, "autotune message backup");
     }
     e = hipMemcpyAsync(save, g->host.m, sizeof(float) * g->M, hipMemcpyDeviceToDevice, st);
-    int rc = e == hipSuccess ? tune_launches(g->dgraph, g->vl, g->fl, damping, temperature, reps, st, best_ms_out)
-                             : hip_error(e, "autotune backup");
+    // the iterations lbp_run_bp runs are timed: a relay graph's variable
+    // launches in that form (one per launch of vl, in its order)
+    std::vector<Launch> &vl = g->relay ? g->relay_vl : g->vl;
+    int rc = e == hipSuccess
+                 ? tune_launches(g->dgraph, g->relay, vl, g->fl, damping, temperature, reps, st, best_ms_out)
+                 : hip_error(e, "autotune backup");
+    for (size_t i = 0; i < g->vl.size(); ++i) g->vl[i].shape = vl[i].shape;
     if (rc == LBP_OK && g->fused)
         rc = tune_fused(g->dgraph, g->fused, 1, g->vl, g->fl, damping, temperature, reps, st, &g->use_fused);
     // loops captured before the shapes and the iteration form changed would
@@ -986,8 +998,9 @@ int lbp_batch_autotune(lbp_batch *b, float damping, float temperature, int32_t r
             e = hipMemcpyAsync(save + off, g->host.m, sizeof(float) * g->M, hipMemcpyDeviceToDevice, st);
         off += g->M;
     }
-    int rc = e == hipSuccess ? tune_launches(b->dgraphs, b->vl, b->fl, damping, temperature, reps, st, nullptr)
-                             : hip_error(e, "autotune backup");
+    int rc = e == hipSuccess
+                 ? tune_launches(b->dgraphs, nullptr, b->vl, b->fl, damping, temperature, reps, st, nullptr)
+                 : hip_error(e, "autotune backup");
     if (rc == LBP_OK && b->fviews)
         rc = tune_fused(b->dgraphs, b->fviews, (int32_t)b->graphs.size(), b->vl, b->fl, damping, temperature, reps,
                         st, &b->use_fused);
