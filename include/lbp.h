@@ -438,7 +438,8 @@ int lbp_graph_set_launch(lbp_graph *g, int32_t i, int32_t waves_per_block, int32
  * gathering their variables' beliefs instead of after (more loads in flight,
  * more registers, fewer wavefronts resident: it pays when the graph streams
  * from HBM rather than sitting in the last-level cache).  Bitwise the same
- * results for every variant. */
+ * results for every variant.  A launch whose shape was set here runs one
+ * wavefront a tile (see lbp_graph_use_automatic). */
 int lbp_graph_set_fused_launch(lbp_graph *g, int32_t i, int32_t waves_per_block, int32_t variant);
 int lbp_autotune(lbp_graph *g, float damping, float temperature, int32_t reps, float *best_ms_out);
 /* Fused iterations: for a graph whose variables all have at most 16 edges and
@@ -448,7 +449,9 @@ int lbp_autotune(lbp_graph *g, float damping, float temperature, int32_t reps, f
  * exact arithmetic; messages alternate between two buffers and always end in
  * the graph's own).  Results are bitwise identical either way; speed depends
  * on the graph and cache sizes, so lbp_autotune switches it on only when it
- * measures faster.  Off by default.  out = {available, in use}. */
+ * measures faster.  Off by default.  Either choice made here holds for
+ * lbp_run_bp, lbp_run_bp_until and records as it stands: the automatic forms
+ * (lbp_graph_use_automatic) are off from then on.  out = {available, in use}. */
 int lbp_graph_use_fused(lbp_graph *g, int enable);
 int lbp_graph_fused_state(const lbp_graph *g, int32_t out[2]);
 /* Resident solver (Sec. "Package features": the same parallel damped
@@ -463,10 +466,43 @@ int lbp_graph_fused_state(const lbp_graph *g, int32_t out[2]);
  * spread over the whole device, so it pays only for the smallest graphs:
  * off by default, lbp_autotune switches it on when it measures faster.
  * Enabling it where it does not apply is LBP_E_INVALID.  Other entry points
- * (batches, lbp_run_bp_until, records) always launch.  out = {applies, in
- * use}. */
+ * (batches, lbp_run_bp_until, records) never use it.  Either choice made here
+ * switches the automatic forms off (lbp_graph_use_automatic).  out =
+ * {applies, in use}. */
 int lbp_graph_use_resident(lbp_graph *g, int enable);
 int lbp_graph_resident_state(const lbp_graph *g, int32_t out[2]);
+/* Automatic forms, on from upload and after lbp_autotune.  With them, runs of
+ * two iterations and more through lbp_run_bp, lbp_run_bp_until and records take
+ * a faster form of the same arithmetic, bitwise the same results, where a rule
+ * on the graph's kind, sizes and temperature finds one:
+ *   one workgroup: a small graph of dense pairwise factors with one state
+ *     count, all of whose variables have at most 64 edges, held on chip for
+ *     all iterations (tables in registers, messages and beliefs in LDS);
+ *   fused three-way: a graph of dense three-way factors (2..4 states, every
+ *     variable of at most 16 edges) in one launch an iteration, as above;
+ *   relay: a graph most of whose variables have two edges, both of OR/AND
+ *     factors, which form those variables' beliefs themselves.
+ * The latter two use a second message buffer, left out where the device has
+ * no room for it at upload (two-phase iterations then).  Disabled, iterations
+ * run as lbp_graph_use_fused and lbp_graph_use_resident say (two-phase where
+ * neither is in use); enabling keeps those two choices for the runs no rule
+ * takes.  This call also says whether fused pairwise launches of few tiles,
+ * variables of at most four edges, run two wavefronts a tile (enabled, as from
+ * upload, and after lbp_autotune) or in their launch shapes (disabled; one
+ * launch: lbp_graph_set_fused_launch). */
+int lbp_graph_use_automatic(lbp_graph *g, int enable);
+/* How lbp_run_bp would run `iters` iterations at this temperature.  out[0]:
+ * LBP_FORM_...; out[1]: the factor launches whose fused variant runs two
+ * wavefronts a tile (bit k: the k-th factor launch).  An odd iteration after
+ * fused or relay pairs runs two-phase. */
+enum {
+    LBP_FORM_TWO_PHASE = 0,
+    LBP_FORM_FUSED = 1,     /* pairwise or three-way */
+    LBP_FORM_RELAY = 2,
+    LBP_FORM_WORKGROUP = 3,
+    LBP_FORM_RESIDENT = 4
+};
+int lbp_graph_form(const lbp_graph *g, int32_t iters, float temperature, int32_t out[2]);
 
 /* Diagnostic timing: runs `reps` launches of one phase of an iteration on the
  * current messages and returns the mean time per launch (per iteration for
@@ -474,8 +510,9 @@ int lbp_graph_resident_state(const lbp_graph *g, int32_t out[2]);
  * stream.  phase 0 = variable (belief) kernels, 1 = factor kernels (in
  * place), 2 = two-phase iterations, 3 = fused iterations (graphs whose
  * variables all have at most 16 edges and 16 states and whose factors are
- * all dense pairwise with equal slot sizes; lbp_run_bp uses them for such
- * graphs, with bitwise the same results).  Phases 1-3 update the messages. */
+ * all dense pairwise with equal slot sizes).  These are the launches one by
+ * one, whatever form lbp_run_bp takes for the graph (lbp_graph_form).  Phases
+ * 1-3 update the messages. */
 int lbp_time_phase(lbp_graph *g, int32_t phase, int32_t reps, float damping, float temperature,
                    float *ms_out);
 

@@ -238,7 +238,11 @@ int lbp_run_bp(lbp_graph *g, int32_t iters, float damping, float temperature) {
 int lbp_graph_use_resident(lbp_graph *g, int enable) {
     if (!g) return fail(LBP_E_INVALID, "graph is NULL");
     if (enable && !g->resident_ok) return fail(LBP_E_INVALID, "the graph does not fit the resident solver");
+    (void)hipSetDevice(g->ctx->device);
+    (void)hipStreamSynchronize(g->ctx->stream);
+    destroy_loops(g->loops);  // captured in an automatic form, perhaps
     g->use_resident = enable != 0;
+    g->automatic = false;
     return LBP_OK;
 }
 
@@ -423,7 +427,7 @@ int lbp_time_phase(lbp_graph *g, int32_t phase, int32_t reps, float damping, flo
     e = hipEventRecord(a, st);
     if (phases & 2) ++g->version;
     if (phase == 2 || phase == 3) {
-        // iterations as lbp_run_bp runs them (phase 3: fused, in pairs)
+        // the launches one by one, no captured loop (phase 3: fused, in pairs)
         if (e == hipSuccess)
             e = launch_loop(g->dgraph, phase == 3 ? g->fused : nullptr, g->vl, g->fl, 2 * reps, P, maxp, st);
         reps *= 2;
@@ -610,6 +614,7 @@ int lbp_graph_set_fused_launch(lbp_graph *g, int32_t i, int32_t waves_per_block,
     (void)hipStreamSynchronize(g->ctx->stream);
     destroy_loops(g->loops);
     g->fl[i - nv].fshape = LaunchShape{waves_per_block, variant & 1, variant >> 1};
+    g->fl[i - nv].plain = true;
     return LBP_OK;
 }
 
@@ -637,6 +642,33 @@ int lbp_graph_use_fused(lbp_graph *g, int enable) {
     (void)hipStreamSynchronize(g->ctx->stream);
     destroy_loops(g->loops);
     g->use_fused = enable != 0;
+    g->automatic = false;
+    return LBP_OK;
+}
+
+int lbp_graph_use_automatic(lbp_graph *g, int enable) {
+    if (!g) return fail(LBP_E_INVALID, "graph is NULL");
+    (void)hipSetDevice(g->ctx->device);
+    (void)hipStreamSynchronize(g->ctx->stream);
+    destroy_loops(g->loops);
+    g->automatic = enable != 0;
+    for (Launch &L : g->fl) L.plain = !enable;
+    return LBP_OK;
+}
+
+int lbp_graph_form(const lbp_graph *g, int32_t iters, float temperature, int32_t out[2]) {
+    if (!g || !out) return fail(LBP_E_INVALID, "graph or out is NULL");
+    std::string why;
+    if (!valid_params(iters, 0.0f, temperature, &why)) return fail(LBP_E_INVALID, why);
+    const DevGraph *views = iters >= 2 ? loop_views(g, temperature) : nullptr;
+    out[0] = g->use_resident                       ? LBP_FORM_RESIDENT
+             : runs_small(g, iters, temperature)   ? LBP_FORM_WORKGROUP
+             : views && views == g->relay          ? LBP_FORM_RELAY
+             : views                               ? LBP_FORM_FUSED
+                                                   : LBP_FORM_TWO_PHASE;
+    out[1] = 0;
+    for (size_t i = 0; i < g->fl.size() && i < 31; ++i)
+        if (g->fl[i].halves() && pair_half_wins(g->fl[i].a, g->fl[i].n, temperature == 0.0f)) out[1] |= 1 << i;
     return LBP_OK;
 }
 
@@ -661,6 +693,8 @@ int lbp_autotune(lbp_graph *g, float damping, float temperature, int32_t reps, f
         (void)hipGetLastError();
         return fail(LBP_E_OOM, "autotune message backup");
     }
+    g->automatic = true;
+    for (Launch &L : g->fl) L.plain = false;
     e = hipMemcpyAsync(save, g->host.m, sizeof(float) * g->M, hipMemcpyDeviceToDevice, st);
     // the iterations lbp_run_bp runs are timed: a relay graph's variable
     // launches in that form (one per launch of vl, in its order)

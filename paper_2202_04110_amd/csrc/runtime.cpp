@@ -223,7 +223,7 @@ hipError_t launch_fused(const DevGraph *view, const std::vector<Launch> &fl, con
     for (const Launch &L : fl)
         if (L.kind != TK_PAIR && (L.kind != TK_GEN || L.a >= 0)) return hipErrorInvalidValue;
     for (const Launch &L : fl) {
-        e = L.kind == TK_PAIR ? launch_pair(view, L.items, L.n, L.a, L.b, maxp, P, L.fshape, st, true, L.half)
+        e = L.kind == TK_PAIR ? launch_pair(view, L.items, L.n, L.a, L.b, maxp, P, L.fshape, st, true, L.halves())
                               : launch_gen(view, L.items, L.n, maxp, P, L.a, st, true);
         if (e != hipSuccess) break;
     }
@@ -653,18 +653,19 @@ static bool tri_fused_wins(const std::vector<Launch> &fl, bool maxp) {
     return true;
 }
 
-static bool runs_small(const lbp_graph *g, int32_t iters, float T) {
-    return g->small.n && iters >= 2 && pair_solve_wins(g->small, T == 0.0f);
+bool runs_small(const lbp_graph *g, int32_t iters, float T) {
+    return g->automatic && g->small.n && iters >= 2 && pair_solve_wins(g->small, T == 0.0f);
 }
 
 const DevGraph *loop_views(const lbp_graph *g, float T) {
     if (g->use_fused) return g->fused;
+    if (!g->automatic) return nullptr;
     if (g->relay) return g->relay;
     return g->tri && tri_fused_wins(g->fl, T == 0.0f) ? g->tri : nullptr;
 }
 
 static const std::vector<Launch> *loop_relay(const lbp_graph *g) {
-    return g->relay && !g->use_fused ? &g->relay_vl : nullptr;
+    return g->relay && g->automatic ? &g->relay_vl : nullptr;
 }
 
 hipError_t run_graph(lbp_graph *g, int32_t iters, float d, float T) {
@@ -888,7 +889,7 @@ int adjoint_backward(lbp_graph *g, const float *grad_q, float *grad_logpot, floa
             for (int32_t j = 0; j + 1 < len && e == hipSuccess; ++j)
                 for (const Launch &L : g->fl)
                     if (e == hipSuccess)
-                        e = launch_pair(J.views + j, L.items, L.n, L.a, L.b, false, P, L.fshape, st, true, L.half);
+                        e = launch_pair(J.views + j, L.items, L.n, L.a, L.b, false, P, L.fshape, st, true, L.halves());
             for (int32_t j = len - 1; j >= 0 && e == hipSuccess; --j) {
                 B.nbar = nbar[cur ^ 1];
                 for (const Launch &L : g->fl)

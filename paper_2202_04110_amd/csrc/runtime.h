@@ -38,7 +38,9 @@ struct Launch {
     int32_t n_mid = 0, n_high = 0;  // variable phase: wavefront- and block-per-variable items after the tiles
     LaunchShape shape;              // chosen by lbp_autotune (variable phase: swizzle only)
     LaunchShape fshape;             // shape of the fused variant of a pairwise launch
-    bool half = false;              // fused: may run two wavefronts a tile
+    bool half = false;              // fused: may run two wavefronts a tile (pair_half_wins decides)
+    bool plain = false;             // fused: one wavefront a tile all the same (its shape was set)
+    bool halves() const { return half && !plain; }
 };
 
 // Host-side launch lists of one graph or of a set of graphs (graph index gi
@@ -134,6 +136,7 @@ struct lbp_graph {
     std::vector<lbp::Launch> relay_vl;  // their variable launches
     lbp::DevGraph *tri = nullptr;     // device [2]: the same of a graph of three-way factors, or null
     bool use_fused = false;           // lbp_run_bp runs fused iterations (chosen by the autotuner)
+    bool automatic = true;            // lbp_run_bp may take the forms chosen by rule (small, tri, relay)
     bool resident_ok = false;         // small enough for the resident solver (plan below)
     bool use_resident = false;        // lbp_run_bp runs the resident solver (chosen by the autotuner)
     lbp::SolvePlan plan;
@@ -231,10 +234,13 @@ bool make_solve_plan(const std::vector<Launch> &vl, const std::vector<Launch> &f
 
 // The same for the solver of small pairwise graphs (PairSolve).
 bool make_pair_solve(const HostLayout &L, int64_t limit_words, PairSolve *plan);
-// `iters` iterations of g on its context's stream as lbp_run_bp runs them:
-// small pairwise graphs in one workgroup, others through run_loop.
+// `iters` iterations of g on its context's stream as lbp_run_bp runs them
+// outside the resident solver: small pairwise graphs in one workgroup, others
+// through run_loop.
 hipError_t run_graph(lbp_graph *g, int32_t iters, float d, float T);
-// The fused views lbp_run_bp uses at temperature T, or nullptr.
+// Whether run_graph takes the one-workgroup solver.
+bool runs_small(const lbp_graph *g, int32_t iters, float T);
+// The fused views its launched iterations use at temperature T, or nullptr.
 const DevGraph *loop_views(const lbp_graph *g, float T);
 // run_graph(iters >= 1), then the residual of the last iteration into out (one
 // float the device can write, page-locked host memory included); mprev: M

@@ -128,6 +128,8 @@ _sig("lbp_graph_use_resident", C.c_int, [_P, C.c_int])
 _sig("lbp_graph_resident_state", C.c_int, [_P, _P])
 _sig("lbp_graph_use_fused", C.c_int, [_P, C.c_int])
 _sig("lbp_graph_fused_state", C.c_int, [_P, _P])
+_sig("lbp_graph_use_automatic", C.c_int, [_P, C.c_int])
+_sig("lbp_graph_form", C.c_int, [_P, C.c_int32, C.c_float, _P])
 _sig("lbp_time_phase", C.c_int, [_P, C.c_int32, C.c_int32, C.c_float, C.c_float, C.POINTER(C.c_float)])
 
 EXPORTS = [n for n in dir(_lib) if n.startswith("lbp_")]
@@ -376,6 +378,22 @@ class Graph:
         st = np.zeros(2, np.int32)
         check(_lib.lbp_graph_fused_state(self.h, _ptr(st)))
         return bool(st[1])
+
+    def use_automatic(self, enable: bool):
+        """The forms chosen by rule (one workgroup, fused three-way, relay): on
+        from upload, off once use_fused or use_resident was called.  Also:
+        fused launches of few tiles with two wavefronts a tile, or in their
+        launch shapes."""
+        check(_lib.lbp_graph_use_automatic(self.h, int(bool(enable))))
+
+    def form(self, iters: int, temperature: float):
+        """(form, halves): how run_bp would run, "two_phase", "fused",
+        "relay", "workgroup" or "resident", and the set of factor launches
+        (counted from 0) whose fused variant runs two wavefronts a tile."""
+        v = np.zeros(2, np.int32)
+        check(_lib.lbp_graph_form(self.h, int(iters), float(temperature), _ptr(v)))
+        return (("two_phase", "fused", "relay", "workgroup", "resident")[int(v[0])],
+                {k for k in range(31) if int(v[1]) >> k & 1})
 
     def use_resident(self, enable: bool):
         """lbp_run_bp in one workgroup with messages in LDS (bitwise the

@@ -69,6 +69,7 @@ def apply_or_tune(graph, damping: float, temperature: float, reps: int = 20, pat
                 graph.set_fused_launch(i, cache[k]["fused_wpb"], cache[k].get("fused_variant", 0))
         if fkey is not None:
             graph.use_fused(cache[fkey]["use"])
+            graph.use_automatic(True)  # the table's choice is for the runs no rule takes
         return {"source": "cache", "shapes": [cache[k] for k in keys],
                 "fused": graph.fused_in_use}
     ms = graph.autotune(damping, temperature, reps)
