@@ -425,7 +425,9 @@ void lbp_server_destroy(lbp_server *s);
  * groups at their current shapes, two passes over the groups; messages saved
  * and restored), so what one phase leaves in the caches for the next counts,
  * and keeps the fastest; best_ms_out (may be NULL) receives, per group, the
- * iteration time with its chosen shape.  lbp_graph_get_launch returns
+ * iteration time with its chosen shape.  Shapes of fused launches are timed
+ * likewise, except of those that run two wavefronts a tile (lbp_graph_form),
+ * which take no shape and keep theirs.  lbp_graph_get_launch returns
  * {phase (0 variable, 1 factor), kind, a, b, waves per block, swizzle, work
  * items, fused waves per block, fused variant} for group i.
  */

@@ -534,7 +534,8 @@ int tune_launches(const DevGraph *gs, const DevGraph *relay, std::vector<Launch>
     return LBP_OK;
 }
 
-// The fused launches' own shapes (waves per block x variant), then fused or
+// The fused launches' own shapes (waves per block x variant; a launch that
+// runs two wavefronts a tile takes none, and keeps what it has), then fused or
 // two-phase iterations, whichever is faster: *use_fused.  gs / fused /
 // stride as for launch_loop.  Moves the messages (the caller restores them).
 int tune_fused(const DevGraph *gs, const DevGraph *fused, int32_t stride, const std::vector<Launch> &vl,
@@ -554,6 +555,7 @@ int tune_fused(const DevGraph *gs, const DevGraph *fused, int32_t stride, const 
         return x;
     };
     for (Launch &L : fl) {
+        if (L.halves() && pair_half_wins(L.a, L.n, maxp)) continue;
         LaunchShape best = L.fshape;
         float best_t = 1e30f;
         for (int w : {1, 2, 4})

@@ -46,6 +46,12 @@ def _load(path):
         return {}
 
 
+def _shapes(graph, cache, keys):
+    """Each launch's entry, with the fused shape it holds where none is recorded."""
+    return [{"fused_wpb": ln["fused_wpb"], "fused_variant": ln["fused_variant"], **cache[k]}
+            for k, ln in zip(keys, graph.launches())]
+
+
 def apply_or_tune(graph, damping: float, temperature: float, reps: int = 20, path=None, device=None,
                   packaged: bool = True):
     """Applies cached shapes to every launch group of ``graph``; runs the
@@ -62,22 +68,28 @@ def apply_or_tune(graph, damping: float, temperature: float, reps: int = 20, pat
     if graph.fused:
         es = max(1, graph.ES)
         fkey = "%s|%s|fused|es2^%d" % (device, "maxprod" if temperature == 0 else "lse", int(math.log2(es)))
-    if all(k in cache for k in keys) and (fkey is None or fkey in cache):
+    # launches with a fused shape: not those that run two wavefronts a tile,
+    # whose recorded shape another graph of the size bucket would take
+    nv = sum(ln["phase"] == 0 for ln in lns)
+    halves = graph.form(2, temperature)[1] if fkey is not None else ()
+    shaped = [fkey is not None and ln["phase"] == 1 and i - nv not in halves for i, ln in enumerate(lns)]
+    if (all(k in cache and (not f or "fused_wpb" in cache[k]) for k, f in zip(keys, shaped)) and
+            (fkey is None or fkey in cache)):
         for i, k in enumerate(keys):
             graph.set_launch(i, cache[k]["wpb"], cache[k]["swizzle"])
-            if fkey is not None and lns[i]["phase"] == 1:
+            if shaped[i]:
                 graph.set_fused_launch(i, cache[k]["fused_wpb"], cache[k].get("fused_variant", 0))
         if fkey is not None:
             graph.use_fused(cache[fkey]["use"])
             graph.use_automatic(True)  # the table's choice is for the runs no rule takes
-        return {"source": "cache", "shapes": [cache[k] for k in keys],
-                "fused": graph.fused_in_use}
+        return {"source": "cache", "shapes": _shapes(graph, cache, keys), "fused": graph.fused_in_use}
     ms = graph.autotune(damping, temperature, reps)
     lns = graph.launches()
     cache = user
-    for k, ln, t in zip(keys, lns, ms):
-        cache[k] = {"wpb": ln["wpb"], "swizzle": ln["swizzle"], "ms": float(t),
-                    "fused_wpb": ln["fused_wpb"], "fused_variant": ln["fused_variant"]}
+    for k, ln, t, f in zip(keys, lns, ms, shaped):
+        entry = cache[k] = dict(cache.get(k, {}), wpb=ln["wpb"], swizzle=ln["swizzle"], ms=float(t))
+        if f or ln["phase"] == 0:
+            entry.update(fused_wpb=ln["fused_wpb"], fused_variant=ln["fused_variant"])
     if fkey is not None:
         cache[fkey] = {"use": graph.fused_in_use}
     try:
@@ -88,4 +100,4 @@ def apply_or_tune(graph, damping: float, temperature: float, reps: int = 20, pat
         os.replace(tmp, path)
     except OSError:
         pass
-    return {"source": "tuned", "shapes": [cache[k] for k in keys], "fused": graph.fused_in_use}
+    return {"source": "tuned", "shapes": _shapes(graph, cache, keys), "fused": graph.fused_in_use}
