@@ -427,7 +427,9 @@ void lbp_server_destroy(lbp_server *s);
  * and keeps the fastest; best_ms_out (may be NULL) receives, per group, the
  * iteration time with its chosen shape.  Shapes of fused launches are timed
  * likewise, except of those that run two wavefronts a tile (lbp_graph_form),
- * which take no shape and keep theirs.  lbp_graph_get_launch returns
+ * which take no shape and keep theirs; and a graph that fits the one-workgroup
+ * form (lbp_graph_use_automatic) is timed in it and launched, and keeps the
+ * faster at temperatures of this kind (zero or above).  lbp_graph_get_launch returns
  * {phase (0 variable, 1 factor), kind, a, b, waves per block, swizzle, work
  * items, fused waves per block, fused variant} for group i.
  */
@@ -479,7 +481,8 @@ int lbp_graph_resident_state(const lbp_graph *g, int32_t out[2]);
  * on the graph's kind, sizes and temperature finds one:
  *   one workgroup: a small graph of dense pairwise factors with one state
  *     count, all of whose variables have at most 64 edges, held on chip for
- *     all iterations (tables in registers, messages and beliefs in LDS);
+ *     all iterations (tables in registers, messages and beliefs in LDS); by
+ *     rule from upload, by timing after lbp_autotune;
  *   fused three-way: a graph of dense three-way factors (2..4 states, every
  *     variable of at most 16 edges) in one launch an iteration, as above;
  *   relay: a graph most of whose variables have two edges, both of OR/AND

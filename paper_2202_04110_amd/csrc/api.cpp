@@ -711,28 +711,49 @@ int lbp_autotune(lbp_graph *g, float damping, float temperature, int32_t reps, f
     // replay the old launches: drop them before timing the launched loop
     (void)hipStreamSynchronize(st);
     destroy_loops(g->loops);
+    // a small pairwise graph in one workgroup, or launched iterations, either
+    // way as lbp_run_bp runs them (a captured loop: captured on the first call
+    // and replayed on the timed one), over enough iterations to hide the
+    // start of a replay
+    const bool maxp = temperature == 0.0f;
+    const int32_t n = std::max(2 * reps, 100);
+    auto time_run = [&](hipEvent_t a, hipEvent_t b, float *ms) {
+        hipError_t x = run_graph(g, n, damping, temperature);
+        if (x == hipSuccess) x = hipEventRecord(a, st);
+        if (x == hipSuccess) x = run_graph(g, n, damping, temperature);
+        if (x == hipSuccess) x = hipEventRecord(b, st);
+        if (x == hipSuccess) x = hipEventSynchronize(b);
+        if (x == hipSuccess) x = hipEventElapsedTime(ms, a, b);
+        return x;
+    };
+    if (rc == LBP_OK && g->small.n) {
+        hipEvent_t a = nullptr, b = nullptr;
+        float t[2] = {0.0f, 0.0f};
+        hipError_t x = hipEventCreate(&a);
+        if (x == hipSuccess) x = hipEventCreate(&b);
+        for (int8_t one = 0; one < 2; ++one) {
+            g->small_timed[maxp] = one;
+            if (x == hipSuccess) x = time_run(a, b, &t[one]);
+        }
+        g->small_timed[maxp] = x == hipSuccess ? t[1] < t[0] : -1;
+        if (a) (void)hipEventDestroy(a);
+        if (b) (void)hipEventDestroy(b);
+        if (x != hipSuccess) rc = hip_error(x, "autotune one workgroup");
+    }
     if (rc == LBP_OK && g->resident_ok) {
-        // the resident solver against the launched iterations chosen above
+        // the resident solver against the iterations chosen above
         const TParams P = make_params(damping, temperature);
-        const bool maxp = temperature == 0.0f;
         hipEvent_t a = nullptr, b = nullptr;
         float tl = 0.0f, tr = 0.0f;
         hipError_t x = hipEventCreate(&a);
         if (x == hipSuccess) x = hipEventCreate(&b);
         if (x == hipSuccess) x = launch_solve_resident(g->dgraph, g->plan, 2, maxp, P, st);  // warm-up
         if (x == hipSuccess) x = hipEventRecord(a, st);
-        if (x == hipSuccess) x = launch_solve_resident(g->dgraph, g->plan, 2 * reps, maxp, P, st);
+        if (x == hipSuccess) x = launch_solve_resident(g->dgraph, g->plan, n, maxp, P, st);
         if (x == hipSuccess) x = hipEventRecord(b, st);
         if (x == hipSuccess) x = hipEventSynchronize(b);
         if (x == hipSuccess) x = hipEventElapsedTime(&tr, a, b);
-        // launched iterations as lbp_run_bp runs them: a captured loop,
-        // captured on the first call and replayed on the timed one
-        if (x == hipSuccess) x = run_graph(g, 2 * reps, damping, temperature);
-        if (x == hipSuccess) x = hipEventRecord(a, st);
-        if (x == hipSuccess) x = run_graph(g, 2 * reps, damping, temperature);
-        if (x == hipSuccess) x = hipEventRecord(b, st);
-        if (x == hipSuccess) x = hipEventSynchronize(b);
-        if (x == hipSuccess) x = hipEventElapsedTime(&tl, a, b);
+        if (x == hipSuccess) x = time_run(a, b, &tl);
         if (a) (void)hipEventDestroy(a);
         if (b) (void)hipEventDestroy(b);
         if (x == hipSuccess) {

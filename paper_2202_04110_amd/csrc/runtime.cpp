@@ -654,7 +654,9 @@ static bool tri_fused_wins(const std::vector<Launch> &fl, bool maxp) {
 }
 
 bool runs_small(const lbp_graph *g, int32_t iters, float T) {
-    return g->automatic && g->small.n && iters >= 2 && pair_solve_wins(g->small, T == 0.0f);
+    if (!g->automatic || !g->small.n || iters < 2) return false;
+    const int8_t timed = g->small_timed[T == 0.0f];
+    return timed >= 0 ? timed != 0 : pair_solve_wins(g->small, T == 0.0f);
 }
 
 const DevGraph *loop_views(const lbp_graph *g, float T) {

@@ -141,6 +141,7 @@ struct lbp_graph {
     bool use_resident = false;        // lbp_run_bp runs the resident solver (chosen by the autotuner)
     lbp::SolvePlan plan;
     lbp::PairSolve small;             // plan of the one-workgroup solver of small pairwise graphs (n = 0: does not apply)
+    int8_t small_timed[2] = {-1, -1};  // the autotuner's choice of it at T > 0 and T = 0 (-1: by rule)
     float *q_tmp = nullptr;           // VS
     int32_t *map_tmp = nullptr;       // V
     std::vector<lbp::Launch> vl, fl;  // the graph's own launches
