@@ -617,24 +617,31 @@ bool make_pair_solve(const HostLayout &L, int64_t limit_words, PairSolve *plan) 
 }
 
 // Where one workgroup beats launched iterations.  Max-product: wherever the
-// graph fits (slowest seen: a 64 x 64 bipartite layer, 4.1 against 4.6 us per
-// iteration; Potts 22 x 22, 8 states 2.3 against 4.4).  Sums: the workgroup's
+// graph fits (slowest seen: a 64 x 64 bipartite layer, 4.2 against 4.5 us per
+// iteration; Potts 22 x 22, 8 states 2.3 against 5.4).  Sums: the workgroup's
 // cycles, estimated from the busiest SIMD's factor tiles (per table entry an
 // add, a subtraction, a multiplication, an exponential and an add, exponentials
-// at a quarter of the rate; the rows' damping) and variable sums, at 3600 of
-// them per us as measured, against what launched iterations take whatever the
-// size of a small graph: 2.9 us and 0.4 more per state above two (fused; the
-// lane's serial chain), 4.5 us for the two launches of a graph with
-// wavefront-path variables.  Measured at T = 1, launched / this, on either
-// side of the line: Potts 24 x 24, 4 states 3.7 / 2.8, 30 x 30 3.8 / 3.9;
-// 20 x 20, 6 states 4.6 / 4.4; 28 x 28, 5 states 4.2 / 5.6; bipartite
-// 50 x 50 4.9 / 3.3, 64 x 64 4.9 / 5.7.
-static bool pair_solve_wins(const PairSolve &S, bool maxp) {
+// at a quarter of the rate; the rows' damping) and variable sums, 3400 of them
+// a us as measured, against what the graph's launched iterations take whatever
+// the size of a small graph: 4.4 us and 0.35 more per state above two in two
+// launches, 2.5 and 0.32 where fused ones are in use (variables of at most
+// four edges, the lane's serial chain; of two, 0.23; fused iterations of more
+// edges take 7 us and up).  Measured at T = 1, two-phase / fused / this (- no
+// such form): Potts 32 x 32, 3 states 4.9 / 2.8 / 2.9; 23 x 23, 4 states 5.2 / 3.1 / 2.8,
+// 26 x 26 5.1 / 3.1 / 3.4; 22 x 22, 5 states 5.7 / 3.4 / 3.3; 18 x 18, 6 states
+// 6.0 / 3.7 / 3.5, 20 x 20 6.1 / 3.7 / 4.4; 16 x 16, 7 states 6.6 / 4.0 / 3.3,
+// 18 x 18 6.6 / 4.1 / 4.6; 16 x 16, 8 states 7.2 / 4.4 / 4.1; chains of 500
+// variables, 6 states 5.3 / 3.3 / 2.5, of 700 5.3 / 3.3 / 3.5; bipartite
+// 56 x 56 4.4 / - / 3.5.
+static bool pair_solve_wins(const PairSolve &S, bool maxp, bool fused) {
     if (maxp) return true;
+    constexpr int64_t kCyclesPerUs = 3400;
     const int64_t n = S.n, tiles = (S.ntiles + 3) / 4, vts = (S.nvt + 3) / 4, mids = (S.nmid + 15) / 16;
     const int64_t tile = 4 * (2 * n * n * 5 + 24 * n) + 16 * (2 * n * n + 2 * n);
     const int64_t cycles = tiles * tile + vts * 4 * n * (6 + 2 * S.maxdeg) + mids * 4 * (60 + 60 * n) + 1000;
-    return cycles < 340 * (S.nmid ? 45 : 29 + 4 * (n - 2));
+    const int64_t launched_ns = fused && S.maxdeg <= 4 ? 2500 + (S.maxdeg <= 2 ? 230 : 320) * (n - 2)
+                                                      : 4400 + 350 * (n - 2);
+    return cycles * 1000 < kCyclesPerUs * launched_ns;
 }
 
 // Fused iterations of three-way graphs gather each variable's messages once
@@ -656,7 +663,7 @@ static bool tri_fused_wins(const std::vector<Launch> &fl, bool maxp) {
 bool runs_small(const lbp_graph *g, int32_t iters, float T) {
     if (!g->automatic || !g->small.n || iters < 2) return false;
     const int8_t timed = g->small_timed[T == 0.0f];
-    return timed >= 0 ? timed != 0 : pair_solve_wins(g->small, T == 0.0f);
+    return timed >= 0 ? timed != 0 : pair_solve_wins(g->small, T == 0.0f, g->use_fused);
 }
 
 const DevGraph *loop_views(const lbp_graph *g, float T) {

@@ -42,7 +42,6 @@ def test_autotune_times_the_workgroup(lbp, ctx, name, T):
     spec = SPECS[name]()
     g = lbp.Graph(ctx, spec)
     other = 0.7 if T == 0.0 else 0.0
-    by_rule = {t: g.form(8, t)[0] for t in (T, other)}
     g.run_bp(20, 0.5, T)
     want = g.get_messages()
     g.reset_messages()
@@ -50,8 +49,13 @@ def test_autotune_times_the_workgroup(lbp, ctx, name, T):
     assert not g.get_messages().any()
     chosen = g.form(8, T)[0]
     assert chosen in ("workgroup", "fused", "two_phase", "resident")
+    rule = lbp.Graph(ctx, spec)  # with the same choice of fused iterations
+    if g.fused:
+        rule.use_fused(g.fused_in_use)
+        rule.use_automatic(True)
     if g.form(8, other)[0] != "resident":  # (that choice holds at every temperature)
-        assert (g.form(8, other)[0] == "workgroup") == (by_rule[other] == "workgroup")
+        assert g.form(8, other)[0] == rule.form(8, other)[0]
+    rule.free()
     g.run_bp(20, 0.5, T)
     np.testing.assert_array_equal(g.get_messages(), want)
     # launched iterations of the same graph
