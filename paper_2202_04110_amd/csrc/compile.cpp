@@ -1062,11 +1062,13 @@ int check_layout(const HostLayout &L, std::string *err) {
             for (int32_t l = 0; l < kLanes; ++l) {
                 const int32_t n = L.vns[(size_t)t * kLanes + l];
                 if (n > vg.bucket || n > vt.n) return oob("lane states exceed bucket/panel");
-                if (!rows_in(vt.b_off + l, n, VB)) return oob("belief-low B/theta");
+                // (a lane without a variable reads what its tile's other lanes do)
+                const int32_t rows = n > 0 ? n : std::min({vt.n, vg.bucket, kLowStatesMax});
+                if (!rows_in(vt.b_off + l, rows, VB)) return oob("belief-low B/theta");
                 for (int32_t k = 0; k < vt.kmax; ++k) {
                     const int64_t ei = vt.e_off + (int64_t)k * kLanes + l;
                     if (!in(ei, (int64_t)L.vedge.size())) return oob("vedge index");
-                    if (!rows_in(L.vedge[ei], n, M)) return oob("belief-low message");
+                    if (!rows_in(L.vedge[ei], rows, M)) return oob("belief-low message");
                 }
             }
         }
@@ -1100,13 +1102,24 @@ int check_layout(const HostLayout &L, std::string *err) {
             if (!(col && L.hedge[k] == -1) && !rows_in(L.hedge[k], h.n, M)) return oob("belief-high message");
     }
     // factor phase
-    auto vb_rows = [&](const FTile &ft, int32_t rows, const int32_t *row_n) -> bool {
-        for (int32_t r = 0; r < rows; ++r)
-            for (int32_t l = 0; l < kLanes; ++l) {
-                const int64_t i = ft.vb_off + (int64_t)r * kLanes + l;
-                if (!in(i, (int64_t)L.fvb.size()) || !rows_in(L.fvb[i], row_n[r], VB)) return false;
+    // belief rows of lanes 0 .. nlanes - 1 inside [0, top): each row's least
+    // and greatest address
+    auto vb_rows_below = [&](const FTile &ft, int32_t rows, const int32_t *row_n, int32_t nlanes, int64_t top) -> bool {
+        for (int32_t r = 0; r < rows; ++r) {
+            const int64_t i = ft.vb_off + (int64_t)r * kLanes;
+            if (i < 0 || i + kLanes > (int64_t)L.fvb.size() || nlanes < 1 || nlanes > kLanes) return false;
+            const int32_t *a = L.fvb.data() + i;
+            int32_t lo = a[0], hi = a[0];
+            for (int32_t l = 1; l < nlanes; ++l) {
+                lo = std::min(lo, a[l]);
+                hi = std::max(hi, a[l]);
             }
+            if (!rows_in(lo, row_n[r], top) || !rows_in(hi, row_n[r], top)) return false;
+        }
         return true;
+    };
+    auto vb_rows = [&](const FTile &ft, int32_t rows, const int32_t *row_n) {
+        return vb_rows_below(ft, rows, row_n, kLanes, VB);
     };
     for (const FGroup &fg : L.fgroups)
         for (int32_t t : fg.tiles) {
@@ -1120,6 +1133,9 @@ int check_layout(const HostLayout &L, std::string *err) {
                 if (ft.a > kPairStatesMax || ft.b > kPairStatesMax) return oob("pair states");
                 if (fg.a != ft.a || fg.b != ft.b) return oob("pair group shape");
                 if (!vb_rows(ft, 2, ns)) return oob("pair belief rows");
+                // (the one-workgroup solver holds the beliefs without the spare panel)
+                if (!vb_rows_below(ft, 2, ns, ft.nact, VB - (int64_t)kLanes * kMaxStates))
+                    return oob("pair slot in the spare panel");
                 if (!in(ft.m_off + (int64_t)(ft.a + ft.b) * kLanes - 1, M)) return oob("pair messages");
                 if (!in(ft.phi_off + (int64_t)ft.a * ft.b * kLanes - 1, P)) return oob("pair potentials");
             } else if (ft.kind == TK_LOGL) {
@@ -1131,7 +1147,7 @@ int check_layout(const HostLayout &L, std::string *err) {
                 const int32_t ch = (ft.a + kLanes - 1) / kLanes;
                 if (ft.a < 2 || ft.a > kLogWaveArityMax || (fg.kind == TK_LOGL && ch > 4))
                     return oob("wave logical arity/bucket");
-                for (int32_t j = 0; j < ft.a; ++j) {
+                for (int32_t j = 0; j < ch * kLanes; ++j) {  // every lane of every chunk reads
                     const int64_t i = ft.vb_off + j;
                     if (!in(i, (int64_t)L.fvb.size()) || !in(L.fvb[i] + kLanes, VB)) return oob("wave logical beliefs");
                 }
@@ -1189,9 +1205,39 @@ int check_layout(const HostLayout &L, std::string *err) {
         for (int32_t a : L.frelay)
             if (a < -1 || (a >= 0 && !in(a >> 1, M))) return oob("relay address");
         if (L.relay_vgroups.size() != L.vgroups.size()) return oob("relay tiles");
+        std::vector<char> summed(L.vtile.size(), 0);
         for (const VGroup &g : L.relay_vgroups)
-            for (int32_t t : g.tiles)
+            for (int32_t t : g.tiles) {
                 if (!in(t, (int64_t)L.vtile.size())) return oob("relay tile");
+                summed[t] = 1;
+            }
+        // an edge of a lane-path variable that no relay launch sums is one of
+        // two edges of logical factors, and its entry names the other
+        std::vector<int32_t> seen(L.V, -1);  // the first such edge's entry
+        std::vector<int32_t> addr(L.V, -1);  // and message address
+        for (const FGroup &fg : L.fgroups)
+            for (int32_t t : fg.tiles) {
+                const FTile &ft = L.ftile[t];
+                const bool wide = ft.kind == TK_LOGW, logical = wide || ft.kind == TK_LOGL;
+                const int32_t slots = ft.kind == TK_PAIR ? 2 : ft.kind == TK_GEN ? L.gcls[ft.a].arity : ft.a;
+                for (int32_t j = 0; j < slots; ++j)
+                    for (int32_t l = 0; l < (wide ? 1 : ft.nact); ++l) {
+                        const int64_t i = ft.vb_off + (wide ? j : (int64_t)j * kLanes + l);
+                        const int32_t v = L.fvar[i], a = L.frelay[i], row = wide ? j / kLanes : j;
+                        if (!in(v, L.V)) return oob("relay slot variable");
+                        const bool relayed = L.vns[v] > 0 && !summed[v / kLanes];
+                        if (relayed != (a >= 0)) return oob("relay entry");
+                        if (!relayed) continue;
+                        if (!logical || L.vns[v] != 2 || !(ft.relay >> row & 1)) return oob("relay row");
+                        const int32_t own = ft.m_off + (wide ? j / kLanes * 2 * kLanes + j % kLanes : 2 * j * kLanes + l);
+                        if (seen[v] < 0) {
+                            seen[v] = a;
+                            addr[v] = own;
+                        } else if (a >> 1 != addr[v] || seen[v] >> 1 != own || (a & 1) == (seen[v] & 1)) {
+                            return oob("relay pair");
+                        }
+                    }
+            }
     }
     if (L.fvar.size() != L.fvb.size()) return oob("fvar size");
     if (L.faff.size() != 2 * L.ftile.size()) return oob("slot base size");
@@ -1204,16 +1250,16 @@ int check_layout(const HostLayout &L, std::string *err) {
             for (int32_t l = 0; l < ft.nact; ++l)
                 if (L.fvar[ft.vb_off + (int64_t)r * kLanes + l] != v0 + l) return oob("slot base");
         }
-    if (L.fusable) {
-        // the fused pairwise kernel recomputes each slot variable's belief from
-        // its edge rows: the variable's tile, lane states and edge addresses
-        // (checked once per variable, then per slot that the variable and its
-        // state count are the tile's)
+    if (L.fusable || L.tri_fusable) {
+        // the fused pairwise and three-way kernels recompute each slot
+        // variable's belief from its edge rows: the variable's tile, lane
+        // states and edge addresses (checked once per variable, then per slot
+        // that the variable and its state count are the tile's)
         std::vector<char> rows_ok(L.V);
         for (int64_t v = 0; v < L.V; ++v) {
             const VTile &vt = L.vtile[v / kLanes];
             const int32_t n = L.vns[v];
-            bool ok = in(vt.b_off + v % kLanes + (int64_t)(n - 1) * kLanes, VB);
+            bool ok = vt.kmax > 0 && in(vt.b_off + v % kLanes + (int64_t)(n - 1) * kLanes, VB);
             for (int32_t k = 0; ok && k < vt.kmax; ++k) {
                 const int64_t ei = vt.e_off + (int64_t)k * kLanes + v % kLanes;
                 ok = in(ei, (int64_t)L.vedge.size()) && in(L.vedge[ei] + (int64_t)(n - 1) * kLanes, M);
@@ -1223,11 +1269,12 @@ int check_layout(const HostLayout &L, std::string *err) {
         for (const FGroup &fg : L.fgroups)
             for (int32_t t : fg.tiles) {
                 const FTile &ft = L.ftile[t];
-                for (int32_t r = 0; r < 2; ++r)
+                if (ft.nact < 1) return oob("empty fused tile");  // idle lanes repeat lane 0
+                for (int32_t r = 0; r < (L.fusable ? 2 : 3); ++r)
                     for (int32_t l = 0; l < ft.nact; ++l) {
                         const int32_t v = L.fvar[ft.vb_off + (int64_t)r * kLanes + l];
                         if (!in(v, L.V)) return oob("fused slot variable");
-                        if (L.vns[v] != (r == 0 ? ft.a : ft.b)) return oob("fused slot states");
+                        if (L.vns[v] != (L.tri_fusable ? -fg.a : r == 0 ? ft.a : ft.b)) return oob("fused slot states");
                         if (!rows_ok[v]) return oob("fused edge rows or evidence");
                     }
             }
