@@ -412,7 +412,7 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
     std::vector<int32_t> eslot(E, -1);  // logical factors' edges: index in fvb
     int64_t M = 0, P = 0;
     auto check = [&](int64_t x, const char *what) {
-        return x < INT32_MAX - 4096 ? LBP_OK : bad(err, std::string(what) + " exceeds 2^31 floats", LBP_E_UNSUPPORTED);
+        return x < kPanelFloatsMax ? LBP_OK : bad(err, std::string(what) + " exceeds 2^31 floats", LBP_E_UNSUPPORTED);
     };
     std::vector<std::pair<int64_t, float>> phi_fill;  // filled after sizing
     // Within a lane-per-factor class, order factors by the 64-variable block
@@ -532,7 +532,9 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
     // tile whose factors so far form one (block, variable offsets) group closes
     // early where that group ends, once 48 lanes are filled: a grid's tiles then
     // each hold one run of horizontal or vertical factors, whose slot variables
-    // are consecutive lanes.  Graphs whose offsets scatter keep full tiles.
+    // are consecutive lanes.  Graphs whose offsets scatter keep full tiles, and
+    // so do three-way classes whose panels might outgrow their indices in
+    // shorter ones.
     auto run_length = [&](const std::vector<int32_t> &facs, size_t i0) {
         auto group = [&](size_t i) {
             return std::make_pair(d->edge_var[d->factor_edge_off[facs[i]]] / kLanes, offsets(facs[i]));
@@ -674,9 +676,10 @@ int compile_desc(const lbp_graph_desc *d_in, HostLayout *L, std::string *err, bo
             // launch groups: dense three-way classes with 2..4 states in every
             // slot run in registers (code -N); the others by LDS need
             const bool tri = tri_class(c);
+            const bool runs = tri && three_way_runs_fit((int64_t)facs.size(), ns[0], M, P);
             grp.a = tri ? -ns[0] : gen_lds_code(gc.ncfg * gc.arity, gc.nrows);
             for (size_t i0 = 0, len = 0; i0 < facs.size(); i0 += len) {
-                len = tri ? run_length(facs, i0) : std::min<size_t>(kLanes, facs.size() - i0);
+                len = runs ? run_length(facs, i0) : std::min<size_t>(kLanes, facs.size() - i0);
                 FTile ft{};
                 ft.kind = TK_GEN;
                 ft.a = gidx;

@@ -100,6 +100,18 @@ struct HostLayout {
     std::vector<VGroup> relay_vgroups;
 };
 
+// Messages and potentials are indexed in 32 bits (a little short of 2^31, for
+// the zero panel).
+constexpr int64_t kPanelFloatsMax = INT32_MAX - 4096;
+
+// Three-way tiles may close at 48 factors where a run of equal offsets ends,
+// up to a third more panel rows: taken where the class's panels, from message
+// offset M and potential offset P on, stay in range at that.
+inline bool three_way_runs_fit(int64_t factors, int32_t states, int64_t M, int64_t P) {
+    const int64_t tiles = (factors + 47) / 48, n = states;
+    return M + tiles * kLanes * 3 * n < kPanelFloatsMax && P + tiles * kLanes * n * n * n < kPanelFloatsMax;
+}
+
 // Returns LBP_OK or an LBP_E_* code with a message in *err.
 // scan_potentials = false leaves the NaN/infinity check of the log-potentials
 // to the caller (compile_desc does it while filling the potential panels).
