@@ -2532,19 +2532,20 @@ hipError_t launch_pair(const DevGraph *gs, const WorkItem *items, int n, int na,
     if (fused && na != 0 && (na != nb || na < 2 || na > kPairStatesMax)) return hipErrorInvalidValue;
     if (fused && half && na != 0 && pair_half_wins(na, n, maxp)) {
         const dim3 grid(blocks_for(2 * n, 4)), block(256);
-#define HALF_CASE(N)                                                                                \
-    case N:                                                                                         \
-        if (maxp) hipLaunchKernelGGL((k_pair_half<N, true>), grid, block, 0, st, gs, items, n, P);  \
-        else hipLaunchKernelGGL((k_pair_half<N, false>), grid, block, 0, st, gs, items, n, P);      \
+#define HALF_CASE(N, MAXP)                                                                   \
+    case MAXP ? -N : N:                                                                      \
+        hipLaunchKernelGGL((k_pair_half<N, MAXP>), grid, block, 0, st, gs, items, n, P);     \
         return hipGetLastError();
-        switch (na) {
-            HALF_CASE(2)
-            HALF_CASE(3)
-            HALF_CASE(4)
-            HALF_CASE(5)
-            HALF_CASE(6)
-            HALF_CASE(7)
-            HALF_CASE(8)
+        switch (maxp ? -na : na) {
+            HALF_CASE(2, false)
+            HALF_CASE(3, false)
+            HALF_CASE(4, false)
+            HALF_CASE(5, false)
+            HALF_CASE(6, false)
+            HALF_CASE(7, false)
+            HALF_CASE(8, false)
+            HALF_CASE(2, true)  // max-product: as pair_half_wins has it
+            HALF_CASE(3, true)
         default: return hipErrorInvalidValue;
         }
 #undef HALF_CASE
