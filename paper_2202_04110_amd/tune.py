@@ -46,10 +46,10 @@ def _load(path):
         return {}
 
 
-def _shapes(graph, cache, keys):
+def _shapes(lns, cache, keys):
     """Each launch's entry, with the fused shape it holds where none is recorded."""
     return [{"fused_wpb": ln["fused_wpb"], "fused_variant": ln["fused_variant"], **cache[k]}
-            for k, ln in zip(keys, graph.launches())]
+            for k, ln in zip(keys, lns)]
 
 
 def apply_or_tune(graph, damping: float, temperature: float, reps: int = 20, path=None, device=None,
@@ -82,7 +82,7 @@ def apply_or_tune(graph, damping: float, temperature: float, reps: int = 20, pat
         if fkey is not None:
             graph.use_fused(cache[fkey]["use"])
             graph.use_automatic(True)  # the table's choice is for the runs no rule takes
-        return {"source": "cache", "shapes": _shapes(graph, cache, keys), "fused": graph.fused_in_use}
+        return {"source": "cache", "shapes": _shapes(lns, cache, keys), "fused": graph.fused_in_use}
     ms = graph.autotune(damping, temperature, reps)
     lns = graph.launches()
     cache = user
@@ -100,4 +100,4 @@ def apply_or_tune(graph, damping: float, temperature: float, reps: int = 20, pat
         os.replace(tmp, path)
     except OSError:
         pass
-    return {"source": "tuned", "shapes": _shapes(graph, cache, keys), "fused": graph.fused_in_use}
+    return {"source": "tuned", "shapes": _shapes(lns, cache, keys), "fused": graph.fused_in_use}
