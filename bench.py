@@ -8,9 +8,11 @@ normalisation fused), then read out normalised beliefs and the MAP into
 device buffers.  K steps are timed between device synchronisations.
 
 Metric: edge-state message updates per second = ES * iters * K / seconds.
-The JSON line also carries the roofline of the dominant kernel (the factor
-phase), timed live with HIP events on the library's stream, and the FP64
-oracle timed on the host's cores on a bounded sample of the same workload.
+The JSON line also carries the roofline of the kernel that a solve spends its
+time in, in the form the library runs the workload (lbp_graph_form), timed
+live: launches with HIP events on the library's stream, forms that only a
+whole run takes by timing runs.  And the FP64 oracle, timed on the host's
+cores on a bounded sample of the same workload.
 """
 from __future__ import annotations
 
@@ -221,6 +223,19 @@ def serving_leg(lbp, W, ctx, n, budgets_mb, seed=5, steps=10, slots=64):
                 1e3 * (summ["p99_s"] or 0), summ["iters_mean"] or 0), file=sys.stderr, flush=True)
         out["budgets"]["%d MB" % budget_mb] = runs
     return out
+
+
+def run_ms(g, iters, d, T, reps):
+    """Mean time of a run of `iters` iterations between device synchronisations."""
+    import torch
+
+    g.run_bp(iters, d, T)
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    for _ in range(reps):
+        g.run_bp(iters, d, T)
+    torch.cuda.synchronize()
+    return (time.perf_counter() - t0) * 1e3 / reps
 
 
 def gradient_leg(lbp, W, ctx, reps=10, side=64, states=6, iters=50, every=10):
@@ -584,7 +599,19 @@ def main():
     t_it = g.time_phase(2, reps, d, T)
     t_fused = g.time_phase(3, reps, d, T) if g.fused else None
     fl = [l for l in g.launches() if l["phase"] == 1]
-    if g.fused and g.fused_in_use:
+    form = g.form(iters, T)[0]
+    if form in ("workgroup", "resident", "relay") or (form == "fused" and not g.fused):
+        # forms that lbp_time_phase does not launch: whole runs
+        t_run = run_ms(g, iters, d, T, max(1, min(10, reps // 10)))
+        kbytes, tkey, shape = bm["floor_bytes"], None, (None, None)
+        kernel, kms = {
+            # one launch reads tables, evidence and messages once and writes the messages once
+            "workgroup": ("whole run in one workgroup (small pairwise graph)", t_run),
+            "resident": ("whole run in one workgroup (resident solver)", t_run),
+            "relay": ("relay iteration (factor launch and the variables it leaves)", t_run / iters),
+            "fused": ("fused iteration (dense three-way factors, beliefs recomputed)", t_run / iters),
+        }[form]
+    elif g.fused and g.fused_in_use:
         # the fused iteration is the dominant (and only) kernel of a solve;
         # it moves the floor bytes: phi, messages in and out, evidence
         kernel, kbytes, kms = "fused iteration (dense pairwise factors, beliefs recomputed)", \
@@ -637,6 +664,7 @@ def main():
                                               "fused_variant")} for l in g.launches()],
         "tune_source": tuned["source"] if tuned else "default",
         "fused_iterations": g.fused_in_use,
+        "form": form,
         "device": tune.device_key(0),
     }
     if args.serving:

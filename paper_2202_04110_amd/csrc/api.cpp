@@ -352,8 +352,10 @@ int lbp_run_bp_until_noalloc(lbp_graph *g, int32_t max_iters, float damping, flo
     g->last_T = temperature;
     int32_t done = 0;
     float r = 0.0f;
-    // the kernels of lbp_run_bp_until, launched one by one (no captured
-    // loop: instantiating one allocates)
+    // two-phase iterations, or fused pairwise ones where they are in use,
+    // launched one by one (no captured loop: instantiating one allocates),
+    // and a two-phase one before every check, whatever form
+    // lbp_run_bp_until takes: the same bits
     while (done < max_iters) {
         const int32_t c = std::min(check_every, max_iters - done);
         hipError_t e = hipSuccess;

@@ -547,8 +547,8 @@ __device__ __forceinline__ void belief_regs3(const GV &G, const int (&v)[3], flo
 
 // mid: lane l holds edge l; a wavefront sum (wave_sum: the same bits in
 // every lane) adds up each state.
-// MU two-state variables a wavefront, their loads in flight together (items
-// i0 .. i0 + MU - 1 of the list, of any graphs); other items one by one.  A
+// kMidGroup two-state variables a wavefront, their loads in flight together
+// (items i0 .. i0 + kMidGroup - 1 of the list, of any graphs); other items one by one.  A
 // wavefront of one variable is a few dozen instructions behind four dependent
 // loads, and a deconvolution graph has thousands: grouped, the launch has a
 // quarter of the wavefronts: 16 deconvolution samples of 200 iterations
@@ -1478,12 +1478,12 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_resident(const DevGraph
 // belief_low_tile, belief_mid_var and pair_tile in their order, so results
 // are bitwise those of launched iterations.
 // Bound by the one compute unit's instruction issue and LDS latency; launched
-// iterations cost 3 us (fused) or 4.5 us (two launches) whatever the size, so
-// small graphs win here (pair_solve_wins draws the line).  Measured per
-// iteration, launched against this: Ising 32 x 32 at T = 0 3.0 / 0.85 us and
-// at T = 1 3.1 / 1.7; Potts 16 x 16, 5 states at T = 1 4.0 / 1.9; chain of 500
-// 4-state variables at T = 1 3.3 / 1.4; bipartite 20 x 20 at T = 0.05
-// 4.4 / 1.4.
+// iterations cost 2.4 us and up (fused) or 4.4 us and up (two launches)
+// whatever the size, so small graphs win here (pair_solve_wins draws the
+// line).  Measured per iteration, two-phase / fused / this: Ising 32 x 32 at
+// T = 0 4.5 / 2.4 / 0.9 us and at T = 1 4.6 / 2.5 / 1.5; Potts 16 x 16, 5
+// states at T = 1 5.6 / 3.3 / 2.0; chain of 500 4-state variables at T = 1
+// 4.5 / 2.8 / 1.4; bipartite 20 x 20 at T = 1 4.2 / - / 1.4.
 template <int N, bool MAXP, int FPT>
 __global__ __launch_bounds__(kPairSolveThreads) void k_solve_pair(const DevGraph *__restrict__ gs, PairSolve S,
                                                                   int iters, TParams P) {
@@ -1838,7 +1838,7 @@ __global__ __launch_bounds__(64) void k_gen_dyn(const DevGraph *__restrict__ gs,
 // each costs 2.5 us and up whatever the size.  Tables (and phibar) are asked
 // for first, and one pass over the edge addresses serves both sums.  Measured
 // on Potts 64 x 64 with 6 states, 50 iterations, checkpoints every 10: a
-// training step 1470 us with four launches a step, 943 now.
+// training step 1470 us with four launches a step, 900 now.
 template <int NA, int NB, bool EXACT, bool FUSED>
 __global__ __launch_bounds__(256) void k_pair_adj(const DevGraph *__restrict__ gs, const WorkItem *__restrict__ items,
                                                   int nitems, TParams P, AdjBufs J) {
