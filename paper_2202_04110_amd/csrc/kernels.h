@@ -49,7 +49,7 @@ struct PairSolve {
     int32_t ntiles, nvt, nmid;   // factor tiles, variable tiles, wavefront-path variables (hvar 0 .. nmid - 1)
     int32_t waves;               // wavefronts of the workgroup
     int32_t M, B, vedge, zero;   // message and belief floats, edge-list entries held in LDS; the zero panel
-    int32_t lds;                 // floats of LDS
+    int32_t lds, lds_limit;      // floats of LDS, and what the device allows
     int32_t maxdeg;              // longest lane-path edge list
 };
 // factor tiles one wavefront can hold (table registers)

@@ -2604,7 +2604,10 @@ static hipError_t pair_solve_launch(const DevGraph *g, const PairSolve &S, int32
     auto go = [&](auto fpt) {
         constexpr int F = decltype(fpt)::value;
         const void *fn = (const void *)k_solve_pair<N, MAXP, F>;
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+        // (the device's limit, not this graph's need: the attribute is the
+        // function's, which threads with other graphs launch too)
+        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)(sizeof(float) * (size_t)S.lds_limit));
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_solve_pair<N, MAXP, F>), dim3(1), dim3(64 * S.waves), shm, st, g, S, iters, P);
         return hipGetLastError();
@@ -2624,7 +2627,7 @@ hipError_t launch_solve_pair(const DevGraph *g, const PairSolve &S, int32_t iter
                              hipStream_t st) {
     if (iters <= 0) return hipSuccess;
     if (S.waves < 1 || S.waves > kPairSolveThreads / 64 || S.nvt > 2 * S.waves || S.M >= 65536 ||
-        S.ntiles > S.waves * pair_solve_tiles_per_wave(S.n) || S.lds != pair_solve_lds(S))
+        S.ntiles > S.waves * pair_solve_tiles_per_wave(S.n) || S.lds != pair_solve_lds(S) || S.lds > S.lds_limit)
         return hipErrorInvalidValue;
     switch (S.n) {
 #define SOLVE_CASE(K) \

@@ -611,7 +611,8 @@ bool make_pair_solve(const HostLayout &L, int64_t limit_words, PairSolve *plan) 
     for (const VTile &vt : L.vtile) S.maxdeg = std::max(S.maxdeg, vt.kmax);
     S.vedge = S.maxdeg > 4 ? (int32_t)L.vedge.size() : 0;
     S.lds = pair_solve_lds(S);
-    if (S.lds > limit_words) return false;
+    S.lds_limit = (int32_t)limit_words;
+    if (S.lds > S.lds_limit) return false;
     *plan = S;
     return true;
 }
