@@ -429,9 +429,10 @@ void lbp_server_destroy(lbp_server *s);
  * likewise, except of those that run two wavefronts a tile (lbp_graph_form),
  * which take no shape and keep theirs; and a graph that fits the one-workgroup
  * form (lbp_graph_use_automatic) is timed in it and launched, and keeps the
- * faster at temperatures of this kind (zero or above).  lbp_graph_get_launch returns
- * {phase (0 variable, 1 factor), kind, a, b, waves per block, swizzle, work
- * items, fused waves per block, fused variant} for group i.
+ * faster (one workgroup near a tie) at temperatures of this kind (zero or
+ * above).  lbp_graph_get_launch returns {phase (0 variable, 1 factor), kind, a, b,
+ * waves per block, swizzle, work items, fused waves per block, fused variant}
+ * for group i.
  */
 int lbp_graph_num_launches(const lbp_graph *g, int32_t *n_out);
 int lbp_graph_get_launch(const lbp_graph *g, int32_t i, int32_t out[9]);

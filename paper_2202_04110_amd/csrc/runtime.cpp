@@ -627,8 +627,13 @@ bool make_pair_solve(const HostLayout &L, int64_t limit_words, PairSolve *plan) 
 // the size of a small graph: 4.4 us and 0.35 more per state above two in two
 // launches, 2.5 and 0.32 where fused ones are in use (variables of at most
 // four edges, the lane's serial chain; of two, 0.23; fused iterations of more
-// edges take 7 us and up).  Measured at T = 1, two-phase / fused / this (- no
-// such form): Potts 32 x 32, 3 states 4.9 / 2.8 / 2.9; 23 x 23, 4 states 5.2 / 3.1 / 2.8,
+// edges take 7 us and up).  Near a tie with fused ones the workgroup is taken
+// (2.8 and 0.27 or 0.16 in the rule): a replay starts 2 us later than one
+// launch, and a new graph's first run captures its loop (24 recorded iterations
+// of a 32 x 32 grid of three states in three segments, with the reverse sweep:
+// 459 us on a new graph in one workgroup, 615 in captured loops).  Measured at
+// T = 1, two-phase / fused / this (- no such form): Ising 42 x 42 4.6 / 2.6 / 2.4, 45 x 45 4.8 / 2.4 / 2.7; Potts
+// 32 x 32, 3 states 4.9 / 2.7 / 2.8; 23 x 23, 4 states 5.2 / 3.1 / 2.8,
 // 26 x 26 5.1 / 3.1 / 3.4; 22 x 22, 5 states 5.7 / 3.4 / 3.3; 18 x 18, 6 states
 // 6.0 / 3.7 / 3.5, 20 x 20 6.1 / 3.7 / 4.4; 16 x 16, 7 states 6.6 / 4.0 / 3.3,
 // 18 x 18 6.6 / 4.1 / 4.6; 16 x 16, 8 states 7.2 / 4.4 / 4.1; chains of 500
@@ -640,7 +645,7 @@ static bool pair_solve_wins(const PairSolve &S, bool maxp, bool fused) {
     const int64_t n = S.n, tiles = (S.ntiles + 3) / 4, vts = (S.nvt + 3) / 4, mids = (S.nmid + 15) / 16;
     const int64_t tile = 4 * (2 * n * n * 5 + 24 * n) + 16 * (2 * n * n + 2 * n);
     const int64_t cycles = tiles * tile + vts * 4 * n * (6 + 2 * S.maxdeg) + mids * 4 * (60 + 60 * n) + 1000;
-    const int64_t launched_ns = fused && S.maxdeg <= 4 ? 2500 + (S.maxdeg <= 2 ? 230 : 320) * (n - 2)
+    const int64_t launched_ns = fused && S.maxdeg <= 4 ? 2800 + (S.maxdeg <= 2 ? 160 : 270) * (n - 2)
                                                       : 4400 + 350 * (n - 2);
     return cycles * 1000 < kCyclesPerUs * launched_ns;
 }

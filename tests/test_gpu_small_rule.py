@@ -24,9 +24,10 @@ def ctx(lbp):
 
 
 # side, states: in one workgroup as uploaded, and with fused iterations in use
-GRIDS = [(38, 2, True, True), (45, 2, True, False), (28, 3, True, True), (36, 3, True, False), (23, 4, True, True),
-         (26, 4, True, False), (20, 5, True, True), (28, 5, False, False), (18, 6, True, True), (20, 6, True, False),
-         (22, 6, True, False), (16, 7, True, True), (18, 7, True, False), (16, 8, True, True), (18, 8, True, False),
+GRIDS = [(38, 2, True, True), (42, 2, True, True), (45, 2, True, False), (32, 3, True, True),
+         (36, 3, True, False), (23, 4, True, True), (26, 4, True, False), (20, 5, True, True),
+         (28, 5, False, False), (18, 6, True, True), (20, 6, True, False), (22, 6, True, False),
+         (16, 7, True, True), (18, 7, True, False), (16, 8, True, True), (18, 8, True, False),
          (22, 8, False, False)]
 
 
