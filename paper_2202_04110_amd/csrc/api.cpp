@@ -235,12 +235,19 @@ int lbp_run_bp(lbp_graph *g, int32_t iters, float damping, float temperature) {
     return LBP_OK;
 }
 
+// Captured loops hold launches as they were: a new choice drops them, once no
+// replay can still run.
+static void drop_loops(lbp_graph *g) {
+    if (g->loops.empty()) return;
+    (void)hipSetDevice(g->ctx->device);
+    (void)hipStreamSynchronize(g->ctx->stream);
+    destroy_loops(g->loops);
+}
+
 int lbp_graph_use_resident(lbp_graph *g, int enable) {
     if (!g) return fail(LBP_E_INVALID, "graph is NULL");
     if (enable && !g->resident_ok) return fail(LBP_E_INVALID, "the graph does not fit the resident solver");
-    (void)hipSetDevice(g->ctx->device);
-    (void)hipStreamSynchronize(g->ctx->stream);
-    destroy_loops(g->loops);  // captured in an automatic form, perhaps
+    drop_loops(g);  // captured in an automatic form, perhaps
     g->use_resident = enable != 0;
     g->automatic = false;
     return LBP_OK;
@@ -614,9 +621,7 @@ int lbp_graph_set_fused_launch(lbp_graph *g, int32_t i, int32_t waves_per_block,
     if (i < nv || i >= nv + nf || !g->fused) return fail(LBP_E_INVALID, "not a launch with a fused variant");
     if (variant < 0 || variant > 3 || (waves_per_block != 1 && waves_per_block != 2 && waves_per_block != 4))
         return fail(LBP_E_INVALID, "waves_per_block must be 1, 2 or 4 and variant 0 to 3");
-    (void)hipSetDevice(g->ctx->device);
-    (void)hipStreamSynchronize(g->ctx->stream);
-    destroy_loops(g->loops);
+    drop_loops(g);
     g->fl[i - nv].fshape = LaunchShape{waves_per_block, variant & 1, variant >> 1};
     g->fl[i - nv].plain = true;
     return LBP_OK;
@@ -631,9 +636,7 @@ int lbp_graph_set_launch(lbp_graph *g, int32_t i, int32_t waves_per_block, int32
     const bool fixed = i < nv || L.kind == TK_GEN;
     if (fixed ? waves_per_block != 4 : (waves_per_block != 1 && waves_per_block != 2 && waves_per_block != 4))
         return fail(LBP_E_INVALID, "waves_per_block must be 1, 2 or 4 (4 for this launch)");
-    (void)hipSetDevice(g->ctx->device);
-    (void)hipStreamSynchronize(g->ctx->stream);
-    destroy_loops(g->loops);
+    drop_loops(g);
     L.shape = LaunchShape{waves_per_block, swizzle};
     if (i < nv && g->relay) g->relay_vl[i].shape = L.shape;
     return LBP_OK;
@@ -642,9 +645,7 @@ int lbp_graph_set_launch(lbp_graph *g, int32_t i, int32_t waves_per_block, int32
 int lbp_graph_use_fused(lbp_graph *g, int enable) {
     if (!g) return fail(LBP_E_INVALID, "graph is NULL");
     if (enable && !g->fused) return fail(LBP_E_INVALID, "the graph has no fused iteration");
-    (void)hipSetDevice(g->ctx->device);
-    (void)hipStreamSynchronize(g->ctx->stream);
-    destroy_loops(g->loops);
+    drop_loops(g);
     g->use_fused = enable != 0;
     g->automatic = false;
     return LBP_OK;
@@ -652,9 +653,7 @@ int lbp_graph_use_fused(lbp_graph *g, int enable) {
 
 int lbp_graph_use_automatic(lbp_graph *g, int enable) {
     if (!g) return fail(LBP_E_INVALID, "graph is NULL");
-    (void)hipSetDevice(g->ctx->device);
-    (void)hipStreamSynchronize(g->ctx->stream);
-    destroy_loops(g->loops);
+    drop_loops(g);
     g->automatic = enable != 0;
     for (Launch &L : g->fl) L.plain = !enable;
     return LBP_OK;

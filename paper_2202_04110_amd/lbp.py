@@ -390,10 +390,10 @@ class Graph:
         """(form, halves): how run_bp would run, "two_phase", "fused",
         "relay", "workgroup" or "resident", and the set of factor launches
         (counted from 0) whose fused variant runs two wavefronts a tile."""
-        v = np.zeros(2, np.int32)
-        check(_lib.lbp_graph_form(self.h, int(iters), float(temperature), _ptr(v)))
-        return (("two_phase", "fused", "relay", "workgroup", "resident")[int(v[0])],
-                {k for k in range(31) if int(v[1]) >> k & 1})
+        v = (C.c_int32 * 2)()
+        check(_lib.lbp_graph_form(self.h, int(iters), float(temperature), v))
+        return (("two_phase", "fused", "relay", "workgroup", "resident")[v[0]],
+                {k for k in range(v[1].bit_length()) if v[1] >> k & 1})
 
     def use_resident(self, enable: bool):
         """lbp_run_bp in one workgroup with messages in LDS (bitwise the
